@@ -92,6 +92,24 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     return wave_reduce_dpp(v, 0.0f, [](float a, float b) { return a + b; });
 }
 
+// Reductions over each row of 16 lanes: pairs, quads (quad permutations), halves and the row
+// (mirrors), i.e. up a binary tree of neighbours; every lane ends with the row's result.
+template <typename Op>
+__device__ __forceinline__ float row16_reduce(float v, Op op) {
+    v = op(v, dpp_move<0xB1, 0xf>(v, v));       // quad_perm [1, 0, 3, 2]
+    v = op(v, dpp_move<0x4E, 0xf>(v, v));       // quad_perm [2, 3, 0, 1]
+    v = op(v, dpp_move<0x141, 0xf>(v, v));      // row_half_mirror
+    return op(v, dpp_move<0x140, 0xf>(v, v));   // row_mirror
+}
+
+__device__ __forceinline__ float row16_max(float v) {
+    return row16_reduce(v, [](float a, float b) { return fmaxf(a, b); });
+}
+
+__device__ __forceinline__ float row16_sum(float v) {
+    return row16_reduce(v, [](float a, float b) { return a + b; });
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

@@ -10,19 +10,42 @@
 //    fp32, so every product is exact in fp64 and the sum's rounding error stays far below the
 //    fp32 rounding of the stored support.  (An fp32 accumulation of a few hundred terms of
 //    magnitude ~10 drifts by ~1e-5, the size of the tolerance on the activities.)
-//  * One workgroup (8 waves) owns one hidden HCU and 16 batch rows, i.e. complete softmax
+//  * One workgroup owns one hidden HCU and kR tiles of 16 batch rows, i.e. complete softmax
 //    segments, so the softmax runs in the epilogue from LDS and the support never round-trips
-//    through HBM.  Wave w computes the 16-column output tiles w, w + 8, ...
-//  * The K dimension is staged through LDS in chunks: the workgroup's weight rows (the active
-//    units' row segments, contiguous M_out floats each) and its 16 x K input panel are loaded
-//    cooperatively, all loads of a chunk in flight together, the next chunk into registers
-//    while the current one feeds the matrix cores.  The chunk is as large as the register and
-//    LDS budget allow (the whole K of the MNIST-shaped layer fits in one).
-//  * Work items (row tile, hidden HCU) are spread over the XCDs so that the row tiles of one
-//    hidden HCU share one XCD's L2 (they read the same weight block).
+//    through HBM.
+//  * A wave owns kTPW tiles of 16 columns; a narrow hidden HCU (few column tiles) also splits its
+//    k-steps over the waves that its columns would leave idle (`parts`), and the shares' fp64 sums
+//    are added through LDS in a fixed order.
+//  * What bounds the short launches is instruction issue, not memory: 64 KiB of weights reach a
+//    CU's LDS in 0.6 us, but an fp64 MFMA takes its SIMD for 64 cycles and no vector instruction
+//    of any wave passes beside it (measured: one conversion per MFMA 71 cycles, five integer
+//    instructions 87, MFMAs alone 65).  So the weight rows go straight to LDS (global_load_lds:
+//    1 KiB per instruction, no registers, no LDS stores) at a row stride kS that is a compile-time
+//    constant, and the operand reads of a run of k-steps need no address arithmetic; the input is
+//    gathered as wide as an input HCU allows (a gather costs a cycle per distinct line) and
+//    converted to fp64 once, on its way into LDS.  The product loop is then the MFMA, one LDS read
+//    of each operand and one conversion per k-step.
+//  * A layer whose active units do not fit one panel streams them in chunks through two stage
+//    buffers, the next chunk's loads in flight during the products.  The buffers are separate
+//    arrays named at compile time, so that the compiler does not make a chunk's LDS reads wait
+//    for the next chunk's loads.
+//  * A batch of many rows takes kR = 4: the weights are then loaded and converted once for four
+//    row tiles, and several workgroups share a CU, so that one's gather, softmax and stores pass
+//    under the others' products.
+//  * For a single row the matrix cores would compute 15 rows of padding: the same lanes then
+//    accumulate their own column and units with fp64 FMAs, and the lane groups are added.
+//  * The softmax of an HCU of up to 128 MCUs takes 16 lanes per row, four rows per wave: a third
+//    of the instructions of one row per wave.
+//  * Measured (MNIST-shaped layer, 156 active units x 100 MCUs x 30 HCUs; before: weights and input
+//    through registers, operand addresses in the product loop): batch 1 8.8 -> 6.3 us, batch 8192
+//    471 -> 270 us (28 TFLOP/s), training batch of 128 12.6 -> 11.9 us; 501 units x 70 MCUs x 17
+//    HCUs at 75 rows 28 -> 20 us; STL-shaped training batch 592 -> 535 us.
+//  * In training, workgroups past the support's split the batch input into the contraction
+//    operands of the trace kernels, 16 rows x 64 columns per wave, beside the support.
 //
 // MFMA f64 16x16x4 lane layout (verified on gfx950): A[i][k] from lane i + 16 k, B[k][j] from
 // lane j + 16 k, and lane l holds D[l / 16 + 4 r][l % 16] in result register r.
+#include <initializer_list>
 #include <mutex>
 #include <type_traits>
 
@@ -33,33 +56,53 @@ namespace bcpnn {
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef int32_t i4 __attribute__((ext_vector_type(4)));
 
-// Buffer resource over [p, p + bytes): loads past the range return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t input_rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+constexpr int kRows = 16;          // batch rows per row tile
+constexpr int kMaxWaves = 16;
+// (row tile, hidden HCU) items from which kR = 4 pays: its workgroups, a quarter of the items, have
+// to fill the CUs (8192 rows x 30 HCUs, 15360 items: 270 us against 430 with kR = 2)
+constexpr int64_t kManyRowTiles = 1024;
+constexpr int kCus = 256;                 // compute units
+constexpr int kMinSplit = 16;             // least workgroups for the input's split
+constexpr int kOneUnits = 1024;           // unit table of the one-chunk variants
+constexpr int kOneBytes = 120 * 1024;     // their panels and table
+constexpr int kManyTiles = 4;             // row tiles per workgroup of the many-rows variant
+// Bytes of a stage buffer: with one row tile the launch has few workgroups and takes most of a CU's
+// LDS (the chunks are then few); with kManyTiles two workgroups share a CU; wide hidden HCUs leave
+// room for the longest unit table.
+constexpr int stage_bytes(int rows, int stride) {
+    return rows > 1 ? 26 * 1024 : stride > 128 ? 36 * 1024 : 73 * 1024;
 }
-
-constexpr int kRows = 16;          // batch rows per workgroup
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kMaxTilesPerWave = 8;   // kWaves * 8 * 16 = 1024 = largest out_mcu
-// Weight vectors staged per thread per chunk (each holds its own address while in flight).
-constexpr int stage_slots(int tiles_per_wave, int vec) {
-    // at least one widest row per thread: M_out <= 128 * tiles_per_wave, 32 lanes per row
-    return vec == 4 ? (tiles_per_wave >= 4 ? 8 : 12) : (tiles_per_wave >= 8 ? 32 : 16);
-}
-constexpr int kXRegs = 8;             // input elements staged per thread per chunk
-constexpr int kLeanSlots = 8;         // weight vectors per thread in the lean variant (see launch)
-constexpr int kRowGroups = kThreads / 32;   // weight rows staged side by side (32 lanes each)
-static_assert(kRowGroups == kRows, "one row group per batch row of the input panel");
+constexpr int kXRegs = 12;                // input elements a thread holds per chunk
 
 struct SupportLayout {
-    int n_tiles, mpad, n_row_tiles;
-    int kc;                        // units per chunk (multiple of 4)
-    int k_alloc;                   // LDS entries of the unit table (>= the largest K_h)
-    int xstride;                   // LDS row stride of the input panel (2 mod 32, see below)
-    bool fits;                     // every thread's share of a chunk fits its staging slots
+    int n_tiles;                   // 16-column tiles of a hidden HCU
+    int groups;                    // waves that share the column tiles (tile t: wave t mod groups)
+    int parts;                     // waves that share a tile's k-steps; groups * parts waves
+    int kc;                        // units per chunk
+    int n_chunks;
+    int k_alloc;                   // unit table: the chunks, the last in whole runs of 64 units
+    int max_k;                     // largest number of active units of a hidden HCU
+    uint32_t mcu_magic;            // ceil(2^32 / in_mcu) (0 for in_mcu = 1)
+    int per;                       // k-steps of a share in a whole chunk
+    int vec4;                      // weight rows move 16 bytes per lane
+    int rw, x_slots;               // input rows per wave, loads per thread and chunk
+    int xstride, mpad;             // LDS row strides of the input panel and the support tile
+    int n_split;                   // workgroups that split the input
+    int sum_order;                 // of the input's column sums
+    int n_row_groups;              // groups of kR row tiles
+    int row_major;                 // workgroup order: hidden HCUs of a row group together
+    int n_main;                    // support workgroups; those past it split the input
+    int n_row_tiles;
 };
+
+typedef void __attribute__((address_space(3))) lds_void;
+
+// A count as a type.
+template <int V>
+struct Count { static constexpr int value = V; };
 
 // Writes the 16 batch entries of unit u in k-step ks (one row tile) as bf16 hi and lo parts
 // (hi = bf16(v), lo = bf16(v - hi), round to nearest even): two 16-byte fragment chunks each.
@@ -97,476 +140,732 @@ __device__ __forceinline__ void write_split_half(const float (&v)[kRows / 2], ui
     *reinterpret_cast<uint4*>(lo + c) = make_uint4(ll[0], ll[1], ll[2], ll[3]);
 }
 
-// kTilesPerWave: 16-column output tiles per wave, ceil(ceil(M_out / 16) / 8).
-// kVec: 4 when weight row segments can be read as float4 (M_out and N_out multiples of 4).
-// kOps: training (the contraction operands are written); the forward pass is a variant of its
-// own, without that code (and, in a kernel trace, under a name of its own).  kStamp: the
-// launch stamps its start and end (training launches that profiling times).
-template <int kTilesPerWave, int kVec, int kLeanSlots, bool kOps, bool kStamp>
-__global__ void __launch_bounds__(kThreads)
+// How the column sums over 16 rows are formed: row by row, the sums of rows 0-7 and 8-15 added, or
+// one or the other by the width of the hidden HCU's share of the input the unit belongs to (an
+// out_hcu-th of the input HCUs; halves up to 256 units).
+enum SumOrder { kRowByRow = 0, kHalves = 1, kByShare = 2 };
+
+// Contraction operands of 16 rows (row tile rt) x 64 columns (pass p, lane = column) of a batch
+// array [B][n], by one wave: each column split into bf16 hi / lo parts in fragment order, plus its
+// sum over these rows.  kPaired (the input, with complement pairs): only the first unit of each
+// input HCU enters the contraction, at the HCU's index (every unit keeps its column sum), and
+// every pair (x_2p, x_2p+1) of these rows must add up to 1: passes start at an even column, so the
+// partner of an even column is the next lane's.  A violation sets the layer's flag.
+// The rows are read through a buffer resource over the batch, so the rows past B read as zero
+// and all 16 loads are unconditional and go out together.  (The launch checks that the offsets
+// fit in 32 bits.)
+__device__ __forceinline__ void split_columns(const Geometry& g, const float* src, int64_t n, int32_t B,
+                                              uint16_t* hi, uint16_t* lo, float* sums, int32_t n_ks,
+                                              bool paired, int32_t* pair_error, int order, int rt,
+                                              int p, int lane) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(src), (short)0, (int)(uint32_t)((int64_t)B * n * 4), 0x00020000);
+    const int64_t i = (int64_t)p * 64 + lane;
+    const bool in = i < n;
+    const int64_t ic = in ? i : n - 1;
+    const int row0 = rt * kRows;
+    float v[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+        v[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+            rs, (uint32_t)(((int64_t)(row0 + r) * n + ic) * 4), 0, 0));
+    float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < kRows / 2; ++r) {
+        s0 += v[r];
+        s1 += v[r + kRows / 2];
+    }
+    float sum = s0 + s1;
+    if (order != kHalves) {
+        float all = s0;
+#pragma unroll
+        for (int r = kRows / 2; r < kRows; ++r) all += v[r];
+        if (order == kRowByRow) {
+            sum = all;
+        } else {
+            const uint32_t ih = (uint32_t)g.in_hcu, oh = (uint32_t)g.out_hcu;   // products < 2^26
+            const uint32_t share = (((uint32_t)ic / g.in_mcu + 1) * oh - 1) / ih;
+            const uint32_t width = ((share + 1) * ih / oh - share * ih / oh) * g.in_mcu;
+            sum = width <= 256 ? sum : all;
+        }
+    }
+    if (paired) {
+        const bool first = in && (i & 1) == 0;
+        bool bad = false;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const float nb = __shfl_down(v[r], 1, 64);
+            bad |= first && row0 + r < B && !(fabsf(v[r] + nb - 1.0f) <= kPairTolerance);
+        }
+        if (bad) *pair_error = 1;
+    }
+    if (in) {
+        if (!paired) write_split_column(v, hi, lo, i, rt, n_ks);
+        else if ((i & 1) == 0) write_split_column(v, hi, lo, i >> 1, rt, n_ks);
+        sums[(int64_t)rt * n + i] = sum;
+    }
+}
+
+__device__ __forceinline__ void split_input(const Geometry& g, const float* x, int32_t B,
+                                            const TraceOperands& ops, int order, int rt, int p,
+                                            int lane) {
+    split_columns(g, x, g.n_in, B, ops.x_hi, ops.x_lo, ops.x_sum, ops.n_ks, ops.paired != 0,
+                  ops.pair_error, order, rt, p, lane);
+}
+
+// kR: row tiles per workgroup.  kV: input elements per load (2 when input HCUs have an even number
+// of MCUs).  kS: row stride of the weight panel in LDS (panel_stride).
+// kMulti: several chunks (else the one chunk holds every active unit).  kFew: a single row, on
+// fp64 FMAs.  kOps: training (the contraction operands are written).  kStamp: the launch stamps
+// its start and end (training launches that profiling times).
+template <int kR, int kS, int kV, bool kMulti, bool kFew, bool kOps, bool kStamp>
+__global__ void __launch_bounds__(64 * kMaxWaves)
 support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32_t B,
                const float* __restrict__ w, const float* __restrict__ bias,
                const int32_t* __restrict__ act_list, const int32_t* __restrict__ act_count,
                float gain, int mode, float* __restrict__ y, float* __restrict__ s,
                int32_t* __restrict__ winner, const float* __restrict__ target,
                TraceOperands ops, unsigned long long* stamp) {
-    constexpr bool has_ops = kOps;
+    constexpr int kTPW = kS <= 256 ? 1 : kS / 256;       // column tiles per wave
+    constexpr bool kNarrow = kS <= 128;
+    constexpr int kStage = !kMulti ? 16 : stage_bytes(kR, kS);
+    __shared__ f4 stage0[kStage / 16];
+    __shared__ f4 stage1[kStage / 16];
+    __shared__ int32_t utab[kMulti ? 4 : kOneUnits];
+    extern __shared__ f4 dyn[];   // the unit table (kMulti) or the panels, then the support tile
     stamp_start<kStamp>(stamp);
     // Highest wave priority: on a CU shared with the silent sweep (second stream), the SIMD
     // arbiter issues this kernel's instructions first.
     __builtin_amdgcn_s_setprio(3);
-    typedef float vec_t __attribute__((ext_vector_type(kVec)));
-    constexpr int kSlots = kLeanSlots > 0 ? kLeanSlots : stage_slots(kTilesPerWave, kVec);
-    extern __shared__ float lds[];
-    const int kc = lay.kc, mpad = lay.mpad, xstride = lay.xstride;
-    int32_t* units = reinterpret_cast<int32_t*>(lds);               // [k_alloc]
-    float* ws = lds + ((lay.k_alloc + 3) & ~3);                      // [kc][mpad]
-    float* xs = ws + (size_t)kc * mpad;                              // [kRows][xstride]
-    float* stile = ws;                                               // [kRows][mpad] afterwards
-
-    const int64_t work = xcd_linear_index(blockIdx.x, (int64_t)lay.n_row_tiles * g.out_hcu);
-    const int hj = (int)(work / lay.n_row_tiles);
-    const int row0 = (int)(work % lay.n_row_tiles) * kRows;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int sub = tid & 31;          // lane within a row group
-    const int grp = tid >> 5;          // row group
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_waves = lay.groups * lay.parts;
+    const int n_thr = 64 * n_waves;
+    if constexpr (kOps) {
+        if ((int)blockIdx.x >= lay.n_main) {
+            const int n_pass = (int)((g.n_in + 63) / 64);
+            const int n_task = n_pass * lay.n_row_tiles;
+            for (int task = ((int)blockIdx.x - lay.n_main) * n_waves + wave; task < n_task;
+                 task += lay.n_split * n_waves)
+                split_input(g, x, B, ops, lay.sum_order, task / n_pass, task % n_pass, lane);
+            stamp_end<kStamp>(stamp);
+            return;
+        }
+    }
+    const int kc = lay.kc, mpad = lay.mpad, xstride = lay.xstride;
+    const int work = (int)xcd_linear_index(blockIdx.x, lay.n_main);
+    const int hj = lay.row_major ? work % g.out_hcu : work / lay.n_row_groups;
+    const int row0 = (lay.row_major ? work / g.out_hcu : work % lay.n_row_groups) * (kR * kRows);
+    const int part = wave / lay.groups, grp = wave - part * lay.groups;
+    const int lg = lane >> 4, lj = lane & 15;
 
     const int32_t k_total = act_count[hj] * g.in_mcu;
     const int32_t* alist = act_list + (int64_t)hj * g.in_hcu;
     const int64_t col_base = (int64_t)hj * g.out_mcu;
-    // The table is filled up to the largest K_h of the layer, so its loads do not wait for the
-    // count; entries past k_total are never used.
-    for (int32_t k = tid; k < lay.k_alloc; k += kThreads)
-        units[k] = (int32_t)((uint32_t)alist[k / g.in_mcu] * (uint32_t)g.in_mcu +
-                             (uint32_t)(k % g.in_mcu));
+    // The table is filled up to the largest K_h of the layer (and past it, with its first entry),
+    // so its loads do not wait for the count; entries past k_total take no part.
+    int32_t* units = kMulti ? reinterpret_cast<int32_t*>(dyn) : utab;
+    const int k_alloc = kMulti ? lay.k_alloc : (kc + 63) & ~63;
+    for (int32_t k = tid; k < k_alloc; k += n_thr) {
+        const int32_t kk = k < lay.max_k ? k : 0;
+        const int32_t h = lay.mcu_magic ? (int32_t)__umulhi((uint32_t)kk, lay.mcu_magic) : kk;
+        units[k] = (alist[h] - h) * g.in_mcu + kk;
+    }
+    // Column of tile t of this wave (a tile past the last repeats it, its result discarded).
+    int col_of[kTPW];
+    float bias_r[kTPW];
+#pragma unroll
+    for (int t = 0; t < kTPW; ++t) {
+        const int nt = grp + t * lay.groups;
+        const int c = (nt < lay.n_tiles ? nt : lay.n_tiles - 1) * 16 + lj;
+        col_of[t] = c < g.out_mcu ? c : g.out_mcu - 1;
+        bias_r[t] = bias[col_base + col_of[t]];
+    }
+    const int x_live = B - row0 < kR * kRows ? B - row0 : kR * kRows;     // rows of this workgroup
     lds_barrier();
 
-    // Weight rows: row group grp takes chunk rows grp, grp + 16, ...; its 32 lanes take the
-    // vectors sub, sub + 32, ... of each row.  Input panel: row r = grp, units sub, sub + 32, ...
-    const int nvec = g.out_mcu / kVec;
-    vec_t wr[kSlots];
-    float xr[kXRegs];
-    // Each thread walks its weight slots in a fixed order: rows grp, grp + 16, ..., and within
-    // a row the vectors sub, sub + 32, ... below nvec (lanes with sub >= nvec stay idle).  The
-    // walk is unrolled over the slots, so every load of a chunk is issued before any is used.
-    auto load_chunk = [&](int32_t k0) {
-        int u = grp, v = sub;
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-            wr[q] = vec_t(0.0f);
-            if (v < nvec && u < kc && k0 + u < k_total) {
-                const vec_t* src =
-                    reinterpret_cast<const vec_t*>(w + (int64_t)units[k0 + u] * g.n_out + col_base);
-                wr[q] = src[v];
-            }
-            v += 32;
-            if (v >= nvec) { v = sub; u += kRowGroups; }
-        }
-        const int64_t xrow = (int64_t)(row0 + grp) * g.n_in;
-        const bool rok = row0 + grp < B;
-#pragma unroll
-        for (int q = 0; q < kXRegs; ++q) {
-            const int uu = sub + 32 * q;
-            xr[q] = (rok && uu < kc && k0 + uu < k_total) ? x[xrow + units[k0 + uu]] : 0.0f;
-        }
-    };
-    auto store_chunk = [&]() {
-        int u = grp, v = sub;
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-            if (v < nvec && u < kc) reinterpret_cast<vec_t*>(ws + u * mpad)[v] = wr[q];
-            v += 32;
-            if (v >= nvec) { v = sub; u += kRowGroups; }
-        }
-#pragma unroll
-        for (int q = 0; q < kXRegs; ++q) {
-            const int uu = sub + 32 * q;
-            if (uu < kc) xs[grp * xstride + uu] = xr[q];
-        }
-    };
-
-    // With one tile per wave, two accumulator chains (even and odd k-steps) keep consecutive
-    // MFMAs independent; with more tiles, the tiles do.
-    constexpr int kChains = kTilesPerWave == 1 ? 2 : 1;
-    d4 acc[kChains][kTilesPerWave];
-#pragma unroll
-    for (int c = 0; c < kChains; ++c)
-#pragma unroll
-        for (int t = 0; t < kTilesPerWave; ++t) acc[c][t] = d4{0.0, 0.0, 0.0, 0.0};
-    // Output tile t of this wave is wave + 8 t; a wave with fewer tiles than kTilesPerWave
-    // repeats its last valid one (same reads, result discarded), so the loop has no branches.
-    int col_of[kTilesPerWave];
-#pragma unroll
-    for (int t = 0; t < kTilesPerWave; ++t) {
-        const int nt = wave + t * kWaves;
-        col_of[t] = (nt < lay.n_tiles ? nt : lay.n_tiles - 1) * 16 + (lane & 15);
-    }
-
-
-    // The input columns [c0, c1) of this workgroup's share of the x operand (see the epilogue),
-    // in passes of 64 columns (lane = column): wave w takes passes 7 - w, 15 - w, ...  A pass
-    // reads each of the 16 rows with one coalesced load (clamped in bounds, zero past the batch
-    // or the range); the first pass is fetched before the softmax so that its latency hides.
-    // (whole input HCUs: with complement pairs both units of a pair fall in one pass)
-    const int64_t c0 = (int64_t)hj * g.in_hcu / g.out_hcu * g.in_mcu;
-    const int64_t c1 = (int64_t)(hj + 1) * g.in_hcu / g.out_hcu * g.in_mcu;
-    const int rows = B - row0 < kRows ? B - row0 : kRows;
-    const int rt = row0 / kRows;
-    const int n_pass = (int)((c1 - c0 + 63) / 64);
-    const int pass0 = kWaves - 1 - wave;
-    float xcol[kRows];
-    // The rows are read through a buffer resource over the batch, so the rows past B read as
-    // zero and all 16 loads are unconditional.  (Clamped to a valid row instead, the loads of
-    // the rows past B shared one value, and the compiler loaded that row first and issued the
-    // others only after it arrived.)  The launch checks that the offsets fit in 32 bits.
-    const __amdgpu_buffer_rsrc_t xrs = input_rsrc(x, (uint32_t)((int64_t)B * g.n_in * 4));
-    auto split_load = [&](int p) {
-        const int64_t i = c0 + (int64_t)p * 64 + lane;
-        const int64_t ic = i < c1 ? i : c1 - 1;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r)
-            xcol[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                xrs, (uint32_t)(((int64_t)(row0 + r) * g.n_in + ic) * 4), 0, 0));
-    };
-    // With complement pairs every pair (x_2p, x_2p+1) of these rows must add up to 1.  The
-    // range starts at an even column and passes are 64 columns wide, so the partner of an even
-    // column is the next lane's column.  A violation sets the layer's flag.
-    auto check_pairs = [&](int p) {
-        const int64_t i = c0 + (int64_t)p * 64 + lane;
-        const bool first = i < c1 && (i & 1) == 0;
-        bool bad = false;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const float nb = __shfl_down(xcol[r], 1, 64);
-            bad |= first && r < rows && !(fabsf(xcol[r] + nb - 1.0f) <= kPairTolerance);
-        }
-        if (bad) *ops.pair_error = 1;
-    };
-    auto split_store = [&](int p) {
-        const int64_t i = c0 + (int64_t)p * 64 + lane;
-        float sum = 0.0f;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            xcol[r] = r < rows ? xcol[r] : 0.0f;
-            sum += xcol[r];
-        }
-        if (ops.paired) check_pairs(p);
-        if (i < c1) {
-            // with complement pairs only the first unit of each input HCU enters the
-            // contraction, at the HCU's index; every unit keeps its column sum
-            if (!ops.paired) write_split_column(xcol, ops.x_hi, ops.x_lo, i, rt, ops.n_ks);
-            else if ((i & 1) == 0) write_split_column(xcol, ops.x_hi, ops.x_lo, i >> 1, rt, ops.n_ks);
-            ops.x_sum[(int64_t)rt * g.n_in + i] = sum;
-        }
-    };
-    // With at most kWaves / 2 passes, each pass is split by two waves, rows 0-7 and 8-15 (task
-    // q = kWaves - 1 - wave: pass q / 2, half q % 2): half the pair checks, conversions and
-    // stores per wave.  The column sum is the two half sums added (as for t), exchanged through
-    // the input panel's LDS, free by then.
-    // (the panel lies past the support tile, which the t split reads meanwhile, when kc >= 16)
-    const bool halves = has_ops && n_pass <= kWaves / 2 && kc >= kRows;
-    const int hq = kWaves - 1 - wave, hpass = hq >> 1, hhalf = hq & 1;
-    const bool hlive = halves && hpass < n_pass;
-    float xh[kRows / 2];
-    auto half_load = [&]() {
-        const int64_t i = c0 + (int64_t)hpass * 64 + lane;
-        const int64_t ic = i < c1 ? i : c1 - 1;
-#pragma unroll
-        for (int r = 0; r < kRows / 2; ++r)
-            xh[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                xrs, (uint32_t)(((int64_t)(row0 + 8 * hhalf + r) * g.n_in + ic) * 4), 0, 0));
-    };
-    float* hsum = xs;                                    // [n_pass][2][64] after the products
-    auto half_store = [&]() {
-        const int64_t i = c0 + (int64_t)hpass * 64 + lane;
-        float sum = 0.0f;
-#pragma unroll
-        for (int r = 0; r < kRows / 2; ++r) {
-            xh[r] = 8 * hhalf + r < rows ? xh[r] : 0.0f;
-            sum += xh[r];
-        }
-        if (ops.paired) {
-            const bool first = i < c1 && (i & 1) == 0;
-            bool bad = false;
-#pragma unroll
-            for (int r = 0; r < kRows / 2; ++r) {
-                const float nb = __shfl_down(xh[r], 1, 64);
-                bad |= first && 8 * hhalf + r < rows && !(fabsf(xh[r] + nb - 1.0f) <= kPairTolerance);
-            }
-            if (bad) *ops.pair_error = 1;
-        }
-        if (i < c1) {
-            if (!ops.paired) write_split_half(xh, ops.x_hi, ops.x_lo, i, rt, hhalf, ops.n_ks);
-            else if ((i & 1) == 0) write_split_half(xh, ops.x_hi, ops.x_lo, i >> 1, rt, hhalf, ops.n_ks);
-        }
-        hsum[(hpass * 2 + hhalf) * 64 + lane] = sum;
-    };
-
-    if (k_total > 0) load_chunk(0);
-    // Bias of this wave's columns, fetched now so that its latency hides behind the contraction
-    // (after the first chunk's loads, which complete first).
-    float bias_r[kTilesPerWave];
-#pragma unroll
-    for (int t = 0; t < kTilesPerWave; ++t) {
-        const int c = col_of[t] < g.out_mcu ? col_of[t] : g.out_mcu - 1;
-        bias_r[t] = bias[col_base + c];
-    }
-    for (int32_t k0 = 0; k0 < k_total; k0 += kc) {
-        lds_barrier();                          // the previous chunk has been consumed
-        store_chunk();
-        lds_barrier();
-        if (k0 + kc < k_total) load_chunk(k0 + kc);   // in flight during the MFMAs below
-        // k-steps of 4 units (the rows beyond k_total hold zeros): groups of 8, then the rest
-        const int rem = k_total - k0 < kc ? k_total - k0 : kc;
-        const int ksteps = (rem + 3) / 4;
-        int ks = 0;
-        for (; ks + 8 <= ksteps; ks += 8) {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int kk = (ks + u) * 4 + (lane >> 4);
-                const double av = (double)xs[(lane & 15) * xstride + kk];
-#pragma unroll
-                for (int t = 0; t < kTilesPerWave; ++t) {
-                    const double bv = (double)ws[kk * mpad + col_of[t]];
-                    acc[u % kChains][t] =
-                        __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[u % kChains][t], 0, 0, 0);
+    // The weight rows of chunk k0 into a stage, [kc][kS], a vector being 16 bytes, or 4 where the
+    // rows are not 16-byte aligned.  Where kS is a multiple of 64, row r is rotated by 16 (r mod 4)
+    // columns, so that the four rows of an operand read fall on different banks.
+    auto request_w_as = [&](int k0, f4* st, auto vec_c) __attribute__((always_inline)) {
+        constexpr int V = decltype(vec_c)::value;
+        constexpr int kRowVecs = kS / V;
+        constexpr bool kRotate = kS % 64 == 0;
+        const int live = k_total - k0 < kc ? k_total - k0 : kc;
+        const uint64_t wb = reinterpret_cast<uint64_t>(w + col_base);
+        const uint32_t row_bytes = (uint32_t)g.n_out * 4u;
+        if constexpr (kRowVecs <= 64) {
+            // one or more whole rows per instruction: wave w takes the 64-vector pieces w,
+            // w + n_waves, ...; a lane keeps its place in the row, its unit is read one piece ahead
+            // (an LDS round trip)
+            constexpr int kRowsPer = 64 / kRowVecs;
+            const int lr = lane / kRowVecs;
+            const int c0 = lr < kRowsPer ? V * (lane - lr * kRowVecs) : kS;   // (kS: an idle lane)
+            char* dst = reinterpret_cast<char*>(st) + 4 * kS * kRowsPer * wave;
+            int r = kRowsPer * wave + lr;
+            const int dr = kRowsPer * n_waves;
+            uint32_t u_next = (uint32_t)units[k0 + (r < live ? r : 0)];
+            for (int first = kRowsPer * wave; first < live; first += dr) {
+                const uint32_t u = u_next;
+                const int c = kRotate ? (c0 - 16 * (r & 3)) & (kS - 1) : c0;
+                const bool in = r < live && c < g.out_mcu;
+                r += dr;
+                u_next = (uint32_t)units[k0 + (r < live ? r : 0)];
+                const char* src = reinterpret_cast<const char*>(
+                    wb + (uint64_t)u * row_bytes + 4u * (uint32_t)c);
+                if (in) {
+                    if constexpr (V == 4)
+                        __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)dst, 16, 0, 0);
+                    else
+                        __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)dst, 4, 0, 0);
                 }
-            }
-        }
-        for (; ks < ksteps; ++ks) {
-            const int kk = ks * 4 + (lane >> 4);
-            const double av = (double)xs[(lane & 15) * xstride + kk];
-#pragma unroll
-            for (int t = 0; t < kTilesPerWave; ++t) {
-                const double bv = (double)ws[kk * mpad + col_of[t]];
-                acc[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[0][t], 0, 0, 0);
-            }
-        }
-    }
-
-    lds_barrier();   // done with the panels; the support tile reuses their LDS
-#pragma unroll
-    for (int t = 0; t < kTilesPerWave; ++t) {
-        const int nt = wave + t * kWaves;
-        if (nt < lay.n_tiles) {
-            const int c = nt * 16 + (lane & 15);
-            if (c < g.out_mcu) {
-                const double bj = (double)bias_r[t];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                {
-                    double v = acc[0][t][r];
-                    if constexpr (kChains == 2) v += acc[1][t][r];
-                    stile[((lane >> 4) + 4 * r) * mpad + c] = (float)(v + bj);
-                }
-            }
-        }
-    }
-    lds_barrier();
-
-    if (hlive) half_load();
-    else if (has_ops && !halves && pass0 < n_pass) split_load(pass0);
-
-    // Each wave takes rows wave and wave + 8 together (independent reduction chains), one LDS
-    // read per element: lane l holds columns l, l + 64, ... of both rows in registers
-    // (M_out <= 128 kTilesPerWave, so 2 kTilesPerWave of them).
-    static_assert(kRows == 2 * kWaves, "two softmax rows per wave");
-    {
-        constexpr int kPer = 2 * kTilesPerWave;
-        const int ra = wave, rb = wave + kWaves;
-        const bool va = row0 + ra < B, vb = row0 + rb < B;
-        float* sa = stile + ra * mpad;
-        float* sb = stile + rb * mpad;
-        const int64_t oa = (int64_t)(row0 + ra) * g.n_out + col_base;
-        const int64_t ob = (int64_t)(row0 + rb) * g.n_out + col_base;
-        float ea[kPer], eb[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int m = lane + 64 * q;
-            ea[q] = m < g.out_mcu ? sa[m] : -INFINITY;
-            eb[q] = m < g.out_mcu ? sb[m] : -INFINITY;
-        }
-        if (s) {
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int m = lane + 64 * q;
-                if (m < g.out_mcu) {
-                    if (va) s[oa + m] = ea[q];
-                    if (vb) s[ob + m] = eb[q];
-                }
-            }
-        }
-        if (mode == 0) {
-            float ma = -INFINITY, mb = -INFINITY;
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                ma = fmaxf(ma, ea[q]);
-                mb = fmaxf(mb, eb[q]);
-            }
-            ma = wave_max_dpp(ma);
-            mb = wave_max_dpp(mb);
-            float da = 0.0f, db = 0.0f;
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const bool in = lane + 64 * q < g.out_mcu;
-                ea[q] = in ? expf(gain * (ea[q] - ma)) : 0.0f;
-                eb[q] = in ? expf(gain * (eb[q] - mb)) : 0.0f;
-                da += ea[q];
-                db += eb[q];
-            }
-            da = wave_sum_dpp(da);
-            db = wave_sum_dpp(db);
-            const float ia = 1.0f / da, ib = 1.0f / db;
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int m = lane + 64 * q;
-                if (m < g.out_mcu) {
-                    const float ya = ea[q] * ia, yb = eb[q] * ib;
-                    sa[m] = ya;                       // kept for the contraction operands
-                    sb[m] = yb;
-                    if (y && va) y[oa + m] = ya;   // training may not ask for them
-                    if (y && vb) y[ob + m] = yb;
-                }
+                dst += 4 * kS * dr;
             }
         } else {
-            float bva = -INFINITY, bvb = -INFINITY;
-            int bia = 0x7fffffff, bib = 0x7fffffff;
+            // several instructions per row: wave w takes the rows w, w + n_waves, ..., whose
+            // addresses are wave-uniform; lane i holds the units of its row i (64 at a time)
+            constexpr int kPieces = (kRowVecs + 63) / 64;
+            for (int first = wave; first < live; first += 64 * n_waves) {
+                const int mine = first + n_waves * lane;
+                const int ul = units[k0 + (mine < live ? mine : 0)];
+                int i = 0;
+                for (int r = first; r < live && i < 64; r += n_waves, ++i) {
+                    uint64_t row = wb + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ul, i) * row_bytes;
+                    asm("" : "+s"(row));                  // in scalar registers
+                    float* dst = reinterpret_cast<float*>(st) + kS * r;
+                    int at0 = V * lane - (kRotate ? 16 * (r & 3) : 0);
+                    if constexpr (kPieces > 1) asm volatile("" : "+v"(at0));
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                const int m = lane + 64 * q;
-                if (m < g.out_mcu && ea[q] > bva) { bva = ea[q]; bia = m; }
-                if (m < g.out_mcu && eb[q] > bvb) { bvb = eb[q]; bib = m; }
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                const float ova = __shfl_xor(bva, off, 64), ovb = __shfl_xor(bvb, off, 64);
-                const int oia = __shfl_xor(bia, off, 64), oib = __shfl_xor(bib, off, 64);
-                if (ova > bva || (ova == bva && oia < bia)) { bva = ova; bia = oia; }
-                if (ovb > bvb || (ovb == bvb && oib < bib)) { bvb = ovb; bib = oib; }
-            }
-            if (lane == 0) {
-                if (va) winner[(int64_t)(row0 + ra) * g.out_hcu + hj] = bia;
-                if (vb) winner[(int64_t)(row0 + rb) * g.out_hcu + hj] = bib;
+                    for (int q = 0; q < kPieces; ++q) {
+                        const int c = kRotate ? (at0 + 64 * V * q) & (kS - 1) : at0 + 64 * V * q;
+                        if (c < g.out_mcu) {
+                            const char* src = reinterpret_cast<const char*>(row) + 4u * (uint32_t)c;
+                            if constexpr (V == 4)
+                                __builtin_amdgcn_global_load_lds(
+                                    (const void*)src, (lds_void*)(dst + 256 * q), 16, 0, 0);
+                            else
+                                __builtin_amdgcn_global_load_lds(
+                                    (const void*)src, (lds_void*)(dst + 64 * q), 4, 0, 0);
+                        }
+                    }
+                }
             }
         }
-    }
-    if (!has_ops) {
-        stamp_end<kStamp>(stamp);
-        return;
-    }
+    };
+    auto request_w = [&](int k0, f4* st) __attribute__((always_inline)) {
+        if (lay.vec4) request_w_as(k0, st, Count<4>{});
+        else request_w_as(k0, st, Count<1>{});
+    };
+    // The input panel [16 kR][xstride] of chunk k0, after the weights: wave w takes rows w,
+    // w + n_waves, ... (rw of them).  With one chunk it is gathered into registers, kV units per
+    // lane in runs of 64 kV, and stored as fp64; slot q is (run q / rw, row q % rw), so that a
+    // row's address is wave-uniform and a run's units are read once.  With several chunks it goes
+    // straight to LDS in fp32 (registers would have to hold it during the products).
+    typedef float xvec __attribute__((ext_vector_type(kV)));
+    constexpr int kSlots = kXRegs / kV;
+    xvec xr[kSlots];
+    auto load_x = [&](int k0) __attribute__((always_inline)) {
+        int i = 0, kb = kV * lane;
+        uint32_t off = 0;
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+            if (q < lay.x_slots) {                                         // uniform
+                if (i == 0) off = (uint32_t)units[k0 + (kb < kc ? kb : 0)] * 4u;
+                int row = wave + n_waves * i;
+                row = row0 + (row < x_live ? row : x_live - 1);
+                const char* xrow = reinterpret_cast<const char*>(x + (int64_t)row * g.n_in);
+                xr[q] = *reinterpret_cast<const xvec*>(xrow + off);
+                if (++i == lay.rw) { i = 0; kb += 64 * kV; }
+            }
+        }
+    };
+    auto store_x = [&](f4* st) __attribute__((always_inline)) {
+        double* xp = reinterpret_cast<double*>(reinterpret_cast<float*>(st) + kc * kS);
+        int i = 0, kb = kV * lane;
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+            if (q < lay.x_slots) {
+                const int row = wave + n_waves * i;
+                if (row < x_live && kb < kc) {
+                    double* dst = xp + row * xstride + kb;
+#pragma unroll
+                    for (int e = 0; e < kV; ++e) dst[e] = (double)xr[q][e];
+                }
+                if (++i == lay.rw) { i = 0; kb += 64 * kV; }
+            }
+        }
+    };
+    auto request_x = [&](int k0, f4* st) __attribute__((always_inline)) {
+        float* xp = reinterpret_cast<float*>(st) + kc * kS;
+        for (int kb = 0; kb < kc; kb += 64) {
+            const uint32_t off = (uint32_t)units[k0 + kb + lane] * 4u;
+            const bool in = kb + lane < kc;
+            for (int row = wave; row < x_live; row += n_waves) {
+                const char* src = reinterpret_cast<const char*>(x + (int64_t)(row0 + row) * g.n_in) + off;
+                if (in) __builtin_amdgcn_global_load_lds((const void*)src,
+                                                         (lds_void*)(xp + row * xstride + kb), 4, 0, 0);
+            }
+        }
+    };
 
-    // Contraction operands of this workgroup's share of the batch (rows row0 .. row0 + 15, one
-    // k-step): the hidden HCU's columns of t (the activity above, or the target) and the input
-    // columns [c0, c1) of x, each column split into bf16 hi / lo parts and written in fragment
-    // order (of x, with complement pairs, the first unit of each input HCU), plus the column
-    // sums over these rows.  Rows past B are written as zeros.
-    // The t columns go out in halves of 8 rows (one 16-byte fragment chunk of hi and of lo per
-    // half), so that 2 M_out threads share the work; the two halves of a column sit in
-    // neighbouring lanes and add their row sums with one lane exchange.
-    lds_barrier();
-    const int n_half = 2 * g.out_mcu;
-    for (int base = 0; base < n_half; base += kThreads) {          // uniform trip count
-        const int q = base + tid;
-        const bool live = q < n_half;
-        const int m = live ? q >> 1 : 0;
-        const int half = q & 1;
-        float v[kRows / 2];
-        float sum = 0.0f;
+    d4 acc[kR][kTPW];
+    double accf[kTPW];
 #pragma unroll
-        for (int i = 0; i < kRows / 2; ++i) {
-            const int r = 8 * half + i;
-            v[i] = live && r < rows
-                       ? (target ? target[(int64_t)(row0 + r) * g.n_out + col_base + m]
-                                 : stile[r * mpad + m])
-                       : 0.0f;
-            sum += v[i];
-        }
-        const float total = sum + __shfl_xor(sum, 1, 64);           // same bits in both lanes
-        if (live) {
-            const int64_t col = col_base + m;
-            write_split_half(v, ops.t_hi, ops.t_lo, col, rt, half, ops.n_ks);
-            if (half == 0) ops.t_sum[(int64_t)rt * g.n_out + col] = total;
-        }
+    for (int t = 0; t < kTPW; ++t) {
+        accf[t] = 0.0;
+#pragma unroll
+        for (int r = 0; r < kR; ++r) acc[r][t] = d4{0.0, 0.0, 0.0, 0.0};
     }
-    if (halves) {
-        if (hlive) half_store();
-        lds_barrier();
-        if (hlive && hhalf == 0) {
-            const int64_t i = c0 + (int64_t)hpass * 64 + lane;
-            if (i < c1)
-                ops.x_sum[(int64_t)rt * g.n_in + i] =
-                    hsum[(hpass * 2) * 64 + lane] + hsum[(hpass * 2 + 1) * 64 + lane];
+    // This wave's k-steps of a chunk are per part .. per part + per - 1 (step ks: lane group lg
+    // holds unit 4 ks + lg).  The operands of kSteps steps are read from LDS together, during the
+    // products of the kSteps before them.
+    constexpr int kSteps = kR * kTPW >= 4 ? 2 : 4;
+    typedef std::conditional_t<kMulti, float, double> xelem;
+    struct Operands {
+        xelem a[kSteps][kR];
+        float b[kSteps][kTPW];
+    };
+    int b_of[kTPW];                        // this lane's column in its rotated rows
+#pragma unroll
+    for (int t = 0; t < kTPW; ++t)
+        b_of[t] = kS % 64 == 0 ? (col_of[t] + 16 * lg) & (kS - 1) : col_of[t];
+    auto read_ops = [&](Operands& o, const xelem* ap, const float* bp, int u0)
+                        __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+#pragma unroll
+            for (int t = 0; t < kTPW; ++t) o.b[u][t] = bp[4 * kS * (u0 + u) + b_of[t]];
+#pragma unroll
+            for (int r = 0; r < kR; ++r) o.a[u][r] = ap[4 * (u0 + u) + r * kRows * xstride];
+        }
+    };
+    auto step = [&](const xelem (&a)[kR], const float (&b)[kTPW]) __attribute__((always_inline)) {
+        double bv[kTPW];
+#pragma unroll
+        for (int t = 0; t < kTPW; ++t) bv[t] = (double)b[t];
+        if constexpr (kFew) {
+#pragma unroll
+            for (int t = 0; t < kTPW; ++t) accf[t] = fma((double)a[0], bv[t], accf[t]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < kR; ++r) {
+                const double av = (double)a[r];
+#pragma unroll
+                for (int t = 0; t < kTPW; ++t)
+                    acc[r][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[t], acc[r][t], 0, 0, 0);
+            }
+        }
+    };
+    auto steps_of = [&](const Operands& o) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) step(o.a[u], o.b[u]);
+    };
+    auto products = [&](int k0, const f4* st) __attribute__((always_inline)) {
+        const int live = k_total - k0 < kc ? k_total - k0 : kc;
+        const int first = lay.per * part;
+        const int all = (live + 3) / 4;
+        const int end = first + lay.per < all ? first + lay.per : all;   // this wave's last step + 1
+        if (first >= end) return;
+        const int last = end == all ? live : 4 * end;                    // its units end here
+        const float* ws = reinterpret_cast<const float*>(st);
+        const xelem* ap = reinterpret_cast<const xelem*>(ws + kc * kS) +
+                          (kFew ? 0 : lj * xstride) + 4 * first + lg;
+        const float* bp = ws + (4 * first + lg) * kS;
+        // the last kSteps steps: those past the end (and units past it) take zeros
+        auto finish = [&](Operands& o, int ks) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < kSteps; ++u) {
+                const bool in = 4 * (ks + u) + lg < last;
+#pragma unroll
+                for (int t = 0; t < kTPW; ++t) o.b[u][t] = in ? o.b[u][t] : 0.0f;
+#pragma unroll
+                for (int r = 0; r < kR; ++r) o.a[u][r] = in ? o.a[u][r] : xelem(0);
+            }
+            steps_of(o);
+        };
+        Operands p, q;               // (reads past the panel after the last step: never used)
+        read_ops(p, ap, bp, 0);
+        int ks = first;
+        for (; ks + 2 * kSteps < end; ks += 2 * kSteps) {
+            read_ops(q, ap, bp, kSteps);
+            steps_of(p);
+            ap += 4 * 2 * kSteps;
+            bp += 4 * kS * 2 * kSteps;
+            read_ops(p, ap, bp, 0);
+            steps_of(q);
+        }
+        if (ks + kSteps < end) {
+            read_ops(q, ap, bp, kSteps);
+            steps_of(p);
+            finish(q, ks + kSteps);
+        } else {
+            finish(p, ks);
+        }
+    };
+
+    if constexpr (kMulti) {
+        // a chunk: its loads have arrived in every wave, the next one's go out (into the buffer
+        // that every wave has finished reading), then its products
+        auto chunk = [&](int c, f4* st, f4* next) __attribute__((always_inline)) {
+            __builtin_amdgcn_s_waitcnt(0);
+            lds_barrier();
+            if ((c + 1) * kc < k_total) {
+                request_w((c + 1) * kc, next);
+                request_x((c + 1) * kc, next);
+            }
+            products(c * kc, st);
+        };
+        request_w(0, stage0);
+        request_x(0, stage0);
+        for (int c = 0; c * kc < k_total; c += 2) {
+            chunk(c, stage0, stage1);
+            if ((c + 1) * kc < k_total) chunk(c + 1, stage1, stage0);
         }
     } else {
-        for (int p = pass0; p < n_pass; p += kWaves) {
-            if (p != pass0) split_load(p);
-            split_store(p);
+        request_w(0, dyn);
+        load_x(0);
+        __builtin_amdgcn_s_waitcnt(0);
+        store_x(dyn);
+        lds_barrier();
+        products(0, dyn);
+    }
+
+    // The support tile [16 kR][mpad] takes the stages (half of its rows in each) or, with one
+    // chunk, the panels' LDS; the shares' sums come after its rows in the first stage (one row
+    // tile) or take the dynamic LDS, the table and panels being done.
+    lds_barrier();
+    float* const tile0 = kMulti ? reinterpret_cast<float*>(stage0) : reinterpret_cast<float*>(dyn);
+    float* const tile1 = kMulti ? reinterpret_cast<float*>(stage1) - 8 * kR * mpad : tile0;
+    auto tile_row = [&](int r) { return (r < 8 * kR ? tile0 : tile1) + r * mpad; };
+    double* red = kMulti && kR == 1 ? reinterpret_cast<double*>(tile0 + 8 * mpad)
+                                    : reinterpret_cast<double*>(reinterpret_cast<float*>(dyn) +
+                                                                (kMulti ? 0 : kR * kRows * mpad));
+    if constexpr (kFew) {
+        // the lane groups' shares of each column
+#pragma unroll
+        for (int t = 0; t < kTPW; ++t) {
+            accf[t] += __shfl_xor(accf[t], 16, 64);
+            accf[t] += __shfl_xor(accf[t], 32, 64);
         }
     }
-    stamp_end<kStamp>(stamp);
+    if (lay.parts > 1) {
+        constexpr int kVals = kFew ? kTPW : 4 * kR * kTPW;     // doubles per lane
+        if (part > 0) {
+            double* mine = red + ((part - 1) * lay.groups + grp) * (kVals * 64) + lane;
+            if constexpr (kFew) {
+#pragma unroll
+                for (int t = 0; t < kTPW; ++t) mine[t * 64] = accf[t];
+            } else {
+#pragma unroll
+                for (int r = 0; r < kR; ++r)
+#pragma unroll
+                    for (int t = 0; t < kTPW; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            mine[((r * kTPW + t) * 4 + e) * 64] = acc[r][t][e];
+            }
+        }
+        lds_barrier();
+        if (part == 0) {
+            for (int p = 1; p < lay.parts; ++p) {
+                const double* from = red + ((p - 1) * lay.groups + grp) * (kVals * 64) + lane;
+                if constexpr (kFew) {
+#pragma unroll
+                    for (int t = 0; t < kTPW; ++t) accf[t] += from[t * 64];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < kR; ++r)
+#pragma unroll
+                        for (int t = 0; t < kTPW; ++t)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc[r][t][e] += from[((r * kTPW + t) * 4 + e) * 64];
+                }
+            }
+        }
+    }
+    if (part == 0) {
+#pragma unroll
+        for (int t = 0; t < kTPW; ++t) {
+            const int c = (grp + t * lay.groups) * 16 + lj;
+            if (c < g.out_mcu) {
+                const double bj = (double)bias_r[t];
+                if constexpr (kFew) {
+                    if (lg == 0) tile0[c] = (float)(accf[t] + bj);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < kR; ++r)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            tile_row(r * kRows + lg + 4 * e)[c] = (float)(acc[r][t][e] + bj);
+                }
+            }
+        }
+    }
+    lds_barrier();
+
+    // Softmax (or argmax) per row: kLanes lanes hold its columns l, l + kLanes, ... (kPer of them,
+    // straight-line; the columns past the last repeat it and take no part).
+    constexpr int kLanes = kNarrow ? 16 : 64;
+    constexpr int kRowsPerWave = 64 / kLanes;
+    const int l = lane & (kLanes - 1);
+    auto activate = [&](auto per_c) __attribute__((always_inline)) {
+        constexpr int kPer = decltype(per_c)::value;
+        for (int rw = wave * kRowsPerWave; rw < x_live; rw += n_waves * kRowsPerWave) {
+            const int row = rw + lane / kLanes;
+            const bool valid = row < x_live;
+            float* sr = tile_row(valid ? row : rw);
+            const int64_t o = (int64_t)(row0 + row) * g.n_out + col_base;
+            float e[kPer];
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int m = l + kLanes * q;
+                e[q] = sr[m < g.out_mcu ? m : g.out_mcu - 1];
+            }
+            if (s) {
+#pragma unroll
+                for (int q = 0; q < kPer; ++q)
+                    if (valid && l + kLanes * q < g.out_mcu) s[o + l + kLanes * q] = e[q];
+            }
+            if (mode == 0) {
+                float mx = e[0];
+#pragma unroll
+                for (int q = 1; q < kPer; ++q) mx = fmaxf(mx, e[q]);
+                mx = kNarrow ? row16_max(mx) : wave_max_dpp(mx);
+#pragma unroll
+                for (int q = 0; q < kPer; ++q)
+                    e[q] = l + kLanes * q < g.out_mcu ? expf(gain * (e[q] - mx)) : 0.0f;
+                // The sum is that of 64 lanes holding columns l, l + 64, ... added up a binary
+                // tree, in both layouts: columns l and l + 64, then four rows of 16 lanes.
+                float d;
+                if constexpr (kNarrow) {
+                    float t4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) t4[q & 3] += e[q];
+#pragma unroll
+                    for (int q = 0; q < (kPer < 4 ? kPer : 4); ++q) t4[q] = row16_sum(t4[q]);
+                    d = (t4[3] + t4[2]) + (t4[1] + t4[0]);
+                } else {
+                    d = 0.0f;
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) d += e[q];
+                    d = wave_sum_dpp(d);
+                }
+                const float inv = 1.0f / d;
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    const int m = l + kLanes * q;
+                    if (valid && m < g.out_mcu) {
+                        const float yv = e[q] * inv;
+                        if constexpr (kOps) sr[m] = yv;   // kept for the contraction operands
+                        if (y) y[o + m] = yv;             // training may not ask for them
+                    }
+                }
+            } else {
+                float bv = -INFINITY;
+                int bi = 0x7fffffff;
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    const int m = l + kLanes * q;
+                    if (m < g.out_mcu && e[q] > bv) { bv = e[q]; bi = m; }
+                }
+                for (int off = kLanes / 2; off > 0; off >>= 1) {
+                    const float ov = __shfl_xor(bv, off, 64);
+                    const int oi = __shfl_xor(bi, off, 64);
+                    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+                }
+                if (valid && l == 0) winner[(int64_t)(row0 + row) * g.out_hcu + hj] = bi;
+            }
+        }
+    };
+    if constexpr (kNarrow) {
+        if (g.out_mcu <= 32) activate(Count<2>{});
+        else if (g.out_mcu <= 64) activate(Count<4>{});
+        else activate(Count<8>{});
+    } else {
+        activate(Count<4 * kTPW>{});
+    }
+    if constexpr (kOps) {
+        // Contraction operands of this workgroup's hidden HCU: its columns of t (the activity
+        // above, or the target), each split into bf16 hi / lo parts in fragment order, plus the
+        // column sums per row tile.  Rows past B are written as zeros.
+        // The columns go out in halves of 8 rows (one 16-byte fragment chunk of hi and of lo per
+        // half), so that 2 M_out threads share a row tile; the two halves of a column sit in
+        // neighbouring lanes and add their row sums with one lane exchange.
+        lds_barrier();
+        const int n_half = 2 * g.out_mcu;
+        const int tiles = (x_live + kRows - 1) / kRows;
+        for (int base = 0; base < n_half * tiles; base += n_thr) {     // uniform trip count
+            const int q = base + tid;
+            const bool live = q < n_half * tiles;
+            const int rtl = kR == 1 || !live ? 0 : q / n_half;         // row tile
+            const int m = live ? (q - rtl * n_half) >> 1 : 0;
+            const int half = q & 1;
+            float v[kRows / 2];
+            float sum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kRows / 2; ++i) {
+                const int r = rtl * kRows + 8 * half + i;
+                v[i] = live && r < x_live
+                           ? (target ? target[(int64_t)(row0 + r) * g.n_out + col_base + m]
+                                     : tile_row(r)[m])
+                           : 0.0f;
+                sum += v[i];
+            }
+            const float total = sum + __shfl_xor(sum, 1, 64);           // same bits in both lanes
+            if (live) {
+                const int64_t col = col_base + m;
+                const int rt = row0 / kRows + rtl;
+                write_split_half(v, ops.t_hi, ops.t_lo, col, rt, half, ops.n_ks);
+                if (half == 0) ops.t_sum[(int64_t)rt * g.n_out + col] = total;
+            }
+        }
+        stamp_end<kStamp>(stamp);
+    }
 }
 
-constexpr size_t kLdsBudget = 120 * 1024;
 constexpr size_t kLdsLimit = 160 * 1024;   // LDS of one gfx950 workgroup
 
-SupportLayout make_layout(const Geometry& g, int32_t B, int32_t max_k, int vec, int lean_slots = 0) {
-    SupportLayout L;
-    L.n_tiles = (g.out_mcu + 15) / 16;
-    // LDS row strides chosen so that the matrix-core operand reads of one half-wave (32 lanes:
-    // 16 rows or columns at two consecutive k) fall on 32 distinct banks: the weight rows at a
-    // stride of 16 mod 32 words, the input panel rows at 2 mod 32.
-    L.mpad = L.n_tiles * 16 + (L.n_tiles % 2 == 0 ? 16 : 0);
-    L.n_row_tiles = (B + kRows - 1) / kRows;
-    L.k_alloc = max_k > 0 ? max_k : 1;
-    // chunk rows such that every thread holds at most `slots` weight vectors
-    const int vec_per_row = (g.out_mcu / vec + 31) / 32;
-    const int tpw = (L.n_tiles + kWaves - 1) / kWaves;
-    const int slots = lean_slots > 0 ? lean_slots
-                                     : stage_slots(tpw <= 1 ? 1 : tpw <= 2 ? 2 : tpw <= 4 ? 4
-                                                                             : kMaxTilesPerWave,
-                                                   vec);
-    const int by_regs_w = kRowGroups * (slots / vec_per_row);
-    const int by_regs_x = 32 * kXRegs;
-    const size_t fixed = (size_t)((L.k_alloc + 3) & ~3) * sizeof(int32_t);
-    const size_t per_unit = (size_t)L.mpad * sizeof(float) + (size_t)kRows * sizeof(float);
-    const int by_lds = (int)((kLdsBudget - fixed - kRows * sizeof(float)) / per_unit);
-    int kc = by_regs_w < by_regs_x ? by_regs_w : by_regs_x;
-    if (by_lds < kc) kc = by_lds;
-    const int need = (max_k + 3) & ~3;
-    if (need < kc) kc = need;
-    kc &= ~3;
-    if (kc < 4) kc = 4;
-    // every thread must hold its share of a chunk: ceil(kc / 16) rows x vec_per_row vectors
-    while (kc > 4 && ((kc + kRowGroups - 1) / kRowGroups) * vec_per_row > slots) kc -= 4;
-    L.kc = kc;
-    L.xstride = ((L.kc + 31) & ~31) + 2;
-    L.fits = ((kc + kRowGroups - 1) / kRowGroups) * vec_per_row <= slots;
-    return L;
+// How a launch covers its rows and units.
+enum Shape { kOneChunk, kChunks, kManyRows, kFewOne, kFewChunks };
+
+constexpr int shape_rows(int v) { return v == kManyRows ? kManyTiles : 1; }
+constexpr bool shape_one(int v) { return v == kOneChunk || v == kFewOne; }
+
+// The weight panel's row stride for M_out columns: 16, 80 (both 16 mod 64, so that the four rows of
+// an operand read fall on different banks), then powers of two.  (A stride per 16 columns would
+// multiply the kernels; between 16 and 80 the launch bounds such HCUs more than their panel.)
+int panel_stride(int out_mcu) {
+    if (out_mcu <= 80) return out_mcu <= 16 ? 16 : 80;
+    int s = 128;
+    while (s < out_mcu) s *= 2;
+    return s;
 }
 
-size_t lds_bytes(const SupportLayout& L) {
-    const size_t table = (size_t)((L.k_alloc + 3) & ~3) * sizeof(int32_t);
-    const size_t panels = (size_t)L.kc * L.mpad * sizeof(float) +
-                          (size_t)kRows * L.xstride * sizeof(float);
-    const size_t tile = (size_t)kRows * L.mpad * sizeof(float);
-    return table + (panels > tile ? panels : tile);
+uint32_t magic_of(int d) { return (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d); }
+
+int input_vec(const Geometry& g) { return g.in_mcu % 2 == 0 ? 2 : 1; }
+
+// Layout of a launch in one shape and its dynamic LDS, or false when the shape does not cover the
+// sizes.
+bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayout* out,
+                 size_t* dyn_bytes) {
+    SupportLayout L{};
+    const int kR = shape_rows(v), ps = panel_stride(g.out_mcu);
+    const int tpw = ps <= 256 ? 1 : ps / 256;
+    if (v != kChunks && ps > 128) return false;
+    L.n_tiles = (g.out_mcu + 15) / 16;
+    L.groups = (L.n_tiles + tpw - 1) / tpw;
+    L.max_k = max_k > 0 ? max_k : 1;
+    L.mcu_magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
+    L.vec4 = g.out_mcu % 4 == 0 && g.n_out % 4 == 0;
+    L.mpad = (g.out_mcu + 15) / 16 * 16 + 4;
+    const int xv = input_vec(g);
+    const int waves = kR == 1 && !shape_one(v) ? kMaxWaves : 8;
+    L.parts = waves / L.groups > 0 ? waves / L.groups : 1;
+    // the chunk; the rows of the input panel lie 4 mod 8 words apart, so that the 16 rows x 4 units
+    // of an operand read fall on different banks
+    auto stride = [v](int kc) {
+        if (shape_one(v)) return (kc + 1) / 2 % 2 ? (kc + 1) / 2 * 2 : (kc + 1) / 2 * 2 + 2;   // fp64
+        return (kc + 3) / 4 % 2 ? (kc + 3) / 4 * 4 : (kc + 3) / 4 * 4 + 4;                     // fp32
+    };
+    const int x_bytes = shape_one(v) ? 8 : 4;              // per element of the input panel
+    auto bytes = [&](int kc) { return 4 * kc * ps + x_bytes * kR * kRows * stride(kc); };
+    L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
+    auto slots = [&](int kc) { return L.rw * ((kc + 64 * xv - 1) / (64 * xv)); };
+    const int most_slots = kXRegs / xv;
+    if (shape_one(v)) {
+        L.kc = (L.max_k + 3) / 4 * 4;
+        if (L.kc > kOneUnits || slots(L.kc) > most_slots || bytes(L.kc) + 4 * kOneUnits > kOneBytes) return false;
+    } else {
+        const int cap = stage_bytes(kR, ps);
+        L.kc = cap / (4 * ps + x_bytes * kR * kRows) / 4 * 4;
+        while (L.kc > 4 && bytes(L.kc) > cap) L.kc -= 4;
+        if (L.kc < 4 || bytes(L.kc) > cap) return false;
+        if (L.kc > (L.max_k + 3) / 4 * 4) L.kc = (L.max_k + 3) / 4 * 4;
+    }
+    L.xstride = stride(L.kc);
+    L.n_chunks = (L.max_k + L.kc - 1) / L.kc;
+    L.k_alloc = (L.kc * (L.n_chunks - 1) + (L.kc + 63) / 64 * 64 + 63) / 64 * 64;
+    const int steps = (L.kc + 3) / 4;                          // no share without a k-step
+    if (L.parts > steps) L.parts = steps;
+    L.per = (steps + L.parts - 1) / L.parts;
+    L.parts = (steps + L.per - 1) / L.per;
+    L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
+    L.x_slots = slots(L.kc);
+    if (shape_one(v) && L.x_slots > most_slots) return false;
+    L.n_row_tiles = (B + kRows - 1) / kRows;
+    L.n_row_groups = (L.n_row_tiles + kR - 1) / kR;
+    L.row_major = !shape_one(v);
+    const int64_t n_main = (int64_t)L.n_row_groups * g.out_hcu;
+    if (n_main > INT32_MAX / 2) return false;
+    L.n_main = (int)n_main;
+    const size_t table = shape_one(v) ? 0 : (size_t)L.k_alloc * 4;
+    const size_t panel = shape_one(v) ? (size_t)bytes(L.kc) : 0;
+    const size_t vals = v == kFewOne || v == kFewChunks ? (size_t)tpw : (size_t)4 * kR * tpw;
+    const size_t tile = (size_t)kR * kRows * L.mpad * sizeof(float);
+    const size_t sums = (size_t)(L.parts - 1) * L.groups * vals * 64 * sizeof(double);
+    const size_t stage = shape_one(v) ? 16 : (size_t)stage_bytes(kR, ps);
+    if (!shape_one(v) && tile / 2 + (kR == 1 ? sums : 0) > stage) return false;
+    const size_t after = shape_one(v) ? tile + sums : kR > 1 ? sums : 0;
+    *dyn_bytes = table + panel > after ? table + panel : after;
+    *out = L;
+    const size_t fixed = 2 * stage + (shape_one(v) ? 4 * kOneUnits : 16);
+    return fixed + *dyn_bytes <= kLdsLimit;
+}
+
+// Calls f with the kernel of a shape, panel stride and input vector.
+template <bool kOps, bool kStamp, typename F>
+hipError_t with_kernel(int shape, int stride, int xv, F&& f) {
+    auto narrow = [&](auto s_c, auto v_c) -> hipError_t {
+        constexpr int S = decltype(s_c)::value, V = decltype(v_c)::value;
+        switch (shape) {
+            case kOneChunk: return f(support_kernel<1, S, V, false, false, kOps, kStamp>);
+            case kChunks: return f(support_kernel<1, S, V, true, false, kOps, kStamp>);
+            case kManyRows: return f(support_kernel<kManyTiles, S, V, true, false, kOps, kStamp>);
+            default: break;
+        }
+        if constexpr (!kOps) {
+            if (shape == kFewOne) return f(support_kernel<1, S, V, false, true, false, false>);
+            if (shape == kFewChunks) return f(support_kernel<1, S, V, true, true, false, false>);
+        }
+        return hipErrorInvalidValue;
+    };
+    auto with_stride = [&](auto v_c) -> hipError_t {
+        constexpr int V = decltype(v_c)::value;
+        switch (stride) {
+            case 16: return narrow(Count<16>{}, v_c);
+            case 80: return narrow(Count<80>{}, v_c);
+            case 128: return narrow(Count<128>{}, v_c);
+            case 256: return f(support_kernel<1, 256, V, true, false, kOps, kStamp>);
+            case 512: return f(support_kernel<1, 512, V, true, false, kOps, kStamp>);
+            case 1024: return f(support_kernel<1, 1024, V, true, false, kOps, kStamp>);
+            default: return hipErrorInvalidValue;
+        }
+    };
+    return xv == 2 ? with_stride(Count<2>{}) : with_stride(Count<1>{});
+}
+
+// Order of the input's column sums.
+int input_sum_order(const Geometry& g, int32_t max_k) {
+    const int64_t narrow = (int64_t)(g.in_hcu / g.out_hcu) * g.in_mcu;    // the narrowest share
+    if (max_k <= 12 || narrow > 256) return kRowByRow;
+    return g.in_hcu % g.out_hcu == 0 || narrow + g.in_mcu <= 256 ? kHalves : kByShare;
 }
 
 // Lets every support variant of one mode take dynamic LDS up to the workgroup's limit.
 template <bool kOps, bool kStamp>
 void raise_lds_limit() {
-    const void* all[] = {(const void*)support_kernel<1, 4, kLeanSlots, kOps, kStamp>,
-                         (const void*)support_kernel<1, 4, 0, kOps, kStamp>,
-                         (const void*)support_kernel<2, 4, 0, kOps, kStamp>,
-                         (const void*)support_kernel<4, 4, 0, kOps, kStamp>,
-                         (const void*)support_kernel<kMaxTilesPerWave, 4, 0, kOps, kStamp>,
-                         (const void*)support_kernel<1, 1, 0, kOps, kStamp>,
-                         (const void*)support_kernel<2, 1, 0, kOps, kStamp>,
-                         (const void*)support_kernel<4, 1, 0, kOps, kStamp>,
-                         (const void*)support_kernel<kMaxTilesPerWave, 1, 0, kOps, kStamp>};
-    for (const void* k : all)
-        (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+    for (int xv = 1; xv <= 2; ++xv)
+        for (int stride : {16, 80, 128, 256, 512, 1024})
+            for (int v = kOneChunk; v <= kFewChunks; ++v)
+                (void)with_kernel<kOps, kStamp>(v, stride, xv, [](auto kernel) {
+                    return hipFuncSetAttribute((const void*)kernel,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)kLdsLimit);
+                });
 }
 
 }  // namespace
@@ -577,19 +876,37 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
                           float* y, float* s, int32_t* winner, const float* target,
                           const TraceOperands* ops, hipEvent_t start, hipEvent_t stop,
                           unsigned long long* stamp) {
-    const int vec = (g.out_mcu % 4 == 0 && g.n_out % 4 == 0) ? 4 : 1;
-    SupportLayout lay = make_layout(g, B, max_active * g.in_mcu, vec);
-    // A layer whose active rows take several chunks anyway stages fewer weight vectors per
-    // thread (kLeanSlots): the kernel then needs few enough registers to share a SIMD with a
-    // workgroup of the tiled silent sweep, which runs beside it on large layers.
-    const bool lean = vec == 4 && lay.n_tiles <= kWaves && lay.kc < max_active * g.in_mcu;
-    if (lean) lay = make_layout(g, B, max_active * g.in_mcu, vec, kLeanSlots);
-    if (!lay.fits) return hipErrorInvalidValue;
+    const int32_t max_k = max_active * g.in_mcu;
+    const int64_t row_tiles = (B + kRows - 1) / kRows;
     // the input rows of the last row tile (up to 15 past B) must have 32-bit byte offsets
-    if ((int64_t)lay.n_row_tiles * kRows * g.n_in * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    const size_t lds = lds_bytes(lay);
-    const int tpw = (lay.n_tiles + kWaves - 1) / kWaves;
-    const int64_t blocks = (int64_t)lay.n_row_tiles * g.out_hcu;
+    if (row_tiles * kRows * g.n_in * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    SupportLayout lay;
+    size_t lds = 0;
+    int shape = -1;
+    auto take = [&](int v) {
+        if (shape < 0 && make_layout(g, B, max_k, v, &lay, &lds)) shape = v;
+    };
+    if (!ops && B == 1) {
+        take(kFewOne);
+        take(kFewChunks);
+    }
+    if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
+    take(kOneChunk);
+    take(kChunks);
+    take(kManyRows);      // (a unit table that leaves no room for the larger stages)
+    if (shape < 0) return hipErrorInvalidValue;
+    const int stride = panel_stride(g.out_mcu), xv = input_vec(g);
+    const int n_waves = lay.groups * lay.parts;
+    int64_t blocks = lay.n_main;
+    lay.sum_order = input_sum_order(g, max_k);
+    if (ops) {
+        // the input's split: a wave per task, or on the CUs that the support leaves idle
+        int64_t n_split = (row_tiles * ((g.n_in + 63) / 64) + n_waves - 1) / n_waves;
+        if (blocks < kCus && n_split > kCus - blocks)
+            n_split = kCus - blocks > kMinSplit ? kCus - blocks : n_split < kMinSplit ? n_split : kMinSplit;
+        lay.n_split = (int)n_split;
+        blocks += n_split;
+    }
     // allow dynamic LDS beyond 64 KB (gfx950 has 160 KB per workgroup): raised once, for
     // every variant a launch can pick, to the largest size a launch can ask for
     static std::once_flag raised;
@@ -599,30 +916,15 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
         raise_lds_limit<true, true>();
         (void)hipGetLastError();
     });
-    auto pick = [&](auto ops_c, auto stamp_c) -> hipError_t {
-        constexpr bool O = decltype(ops_c)::value, S = decltype(stamp_c)::value;
-        auto go = [&](auto kernel) {
-            const TraceOperands o = ops ? *ops : TraceOperands{};
-            // the events (when given) are recorded around the launch
-            return launch_timed(kernel, dim3((unsigned)blocks), dim3(kThreads), lds, stream,
-                                start, stop, g, lay, x, B, w, bias, act_list, act_count, gain,
-                                mode, y, s, winner, target, o, stamp);
-        };
-        if (vec == 4) {
-            if (lean) return go(support_kernel<1, 4, kLeanSlots, O, S>);
-            if (tpw <= 1) return go(support_kernel<1, 4, 0, O, S>);
-            if (tpw <= 2) return go(support_kernel<2, 4, 0, O, S>);
-            if (tpw <= 4) return go(support_kernel<4, 4, 0, O, S>);
-            return go(support_kernel<kMaxTilesPerWave, 4, 0, O, S>);
-        }
-        if (tpw <= 1) return go(support_kernel<1, 1, 0, O, S>);
-        if (tpw <= 2) return go(support_kernel<2, 1, 0, O, S>);
-        if (tpw <= 4) return go(support_kernel<4, 1, 0, O, S>);
-        return go(support_kernel<kMaxTilesPerWave, 1, 0, O, S>);
+    const TraceOperands o = ops ? *ops : TraceOperands{};
+    // the events (when given) are recorded around the launch
+    auto go = [&](auto kernel) {
+        return launch_timed(kernel, dim3((unsigned)blocks), dim3(64 * n_waves), lds, stream, start,
+                            stop, g, lay, x, B, w, bias, act_list, act_count, gain, mode, y, s,
+                            winner, target, o, stamp);
     };
-    if (!ops) return stamp ? hipErrorInvalidValue : pick(std::false_type{}, std::false_type{});
-    return stamp ? pick(std::true_type{}, std::true_type{})
-                 : pick(std::true_type{}, std::false_type{});
+    if (!ops) return stamp ? hipErrorInvalidValue : with_kernel<false, false>(shape, stride, xv, go);
+    return stamp ? with_kernel<true, true>(shape, stride, xv, go) : with_kernel<true, false>(shape, stride, xv, go);
 }
 
 }  // namespace bcpnn

@@ -1,0 +1,71 @@
+"""GPU: the support's launch shapes (one chunk, chunks, many rows, a single row) at the
+edges of their column tiles, unit chunks and input vectors, against the oracle's forward pass on a
+given state."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2106_05373_amd import synth
+from pairs import TOL_ACT, Pair, assert_support_close, gpu_config, max_abs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    print(f"\n[gpu] {request.node.nodeid}", file=sys.stderr, flush=True)
+    yield
+
+
+def given_state(rng, hin, min_, hout, mout, mask):
+    n_in, n_out = hin * min_, hout * mout
+    w = rng.normal(0, 0.7, (n_in, n_out)).astype(np.float32)
+    w *= np.repeat(np.repeat(mask, min_, 0), mout, 1)
+    pj = rng.random(n_out).astype(np.float32) + 0.1
+    return dict(pi=np.full(n_in, 1 / min_, np.float32), pj=pj,
+                pij=np.full((n_in, n_out), 1e-3, np.float32), w=w,
+                b=np.log(pj).astype(np.float32), mask=mask)
+
+
+# (in_hcu, in_mcu, out_hcu, out_mcu, active input HCUs, batch)
+SHAPES = [
+    # one chunk: column tiles 1, 5 (16-byte rows and not), 7, 8; odd and even MCUs per input HCU
+    (20, 2, 3, 16, 9, 33), (20, 1, 2, 17, 13, 16), (31, 3, 3, 70, 11, 20), (40, 2, 2, 80, 31, 17),
+    (40, 4, 2, 81, 20, 5), (90, 2, 3, 100, 78, 129), (60, 2, 2, 128, 50, 31),
+    # a single row: one chunk, chunks
+    (90, 2, 3, 100, 78, 1), (300, 3, 2, 70, 201, 1), (400, 2, 2, 12, 400, 1),
+    # chunks: a partial last one, unit counts one past a chunk, every panel stride
+    (300, 3, 2, 70, 201, 40), (700, 1, 3, 6, 613, 18), (600, 2, 2, 100, 599, 20),
+    (200, 2, 2, 129, 151, 17), (150, 3, 2, 257, 99, 16), (100, 2, 2, 513, 61, 18),
+    # many rows: groups of four row tiles, the last one partial
+    (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
+    # more active units than the larger stages leave room for in the unit table
+    (6000, 2, 1, 40, 5900, 18), (12288, 1, 2, 20, 12288, 3),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_forward_and_readout_match_oracle(shape):
+    hin, min_, hout, mout, k, B = shape
+    rng = np.random.default_rng(hin * 7 + mout)
+    mask = np.stack([synth.random_mask(hin, 1, k, 50 + c)[:, 0] for c in range(hout)], 1)
+    if hout > 1 and k > 2:                       # hidden HCUs of unequal counts
+        mask[np.flatnonzero(mask[:, -1])[1], -1] = 0
+    pair = Pair(gpu_config(hin, min_, hout, mout, B, gain=2.0), mask)
+    pair.ora.set_state(given_state(rng, hin, min_, hout, mout, mask))
+    pair.sync_gpu_to_oracle()
+    a = rng.random((B, hin, min_)) + 0.05
+    x = (a / a.sum(-1, keepdims=True)).reshape(B, -1).astype(np.float32)
+    y, s, y_o, s_o = pair.forward(x)
+    # supports near zero: fp64 sums in another order differ by 2^-53 of their terms, not of s
+    far = np.abs(s_o) > 1e-6
+    assert_support_close(s[far], s_o[far])
+    assert max_abs(s[~far], s_o[~far]) <= 1e-11
+    assert max_abs(y, y_o) <= TOL_ACT
+    t = pair.torch
+    win = t.empty((B, hout), device="cuda", dtype=t.int32)
+    pair.gpu.readout(pair.dev(x), win)
+    best = s.reshape(B, hout, mout).argmax(2)    # the argmax of the GPU's own support: exact
+    assert np.array_equal(win.cpu().numpy(), best)
+    pair.close()
