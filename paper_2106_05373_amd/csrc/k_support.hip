@@ -213,6 +213,29 @@ __device__ __forceinline__ void split_input(const Geometry& g, const float* x, i
                   ops.pair_error, order, rt, p, lane);
 }
 
+// Training with a target whose activities nobody asked for: the traces take the target, so the
+// support and its softmax would go nowhere.  Only the operands are written: the input's, then the
+// target's, a wave per 16 rows x 64 columns.
+template <bool kStamp>
+__global__ void __launch_bounds__(256)
+split_kernel(Geometry g, const float* __restrict__ x, int32_t B, const float* __restrict__ target,
+             TraceOperands ops, int order, unsigned long long* stamp) {
+    stamp_start<kStamp>(stamp);
+    __builtin_amdgcn_s_setprio(3);
+    const int lane = threadIdx.x & 63;
+    const int task = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int px = (int)((g.n_in + 63) / 64), pt = (int)((g.n_out + 63) / 64);
+    const int tiles = (B + kRows - 1) / kRows;
+    if (task < px * tiles) {
+        split_input(g, x, B, ops, order, task / px, task % px, lane);
+    } else if (task < (px + pt) * tiles) {
+        const int t = task - px * tiles;
+        split_columns(g, target, g.n_out, B, ops.t_hi, ops.t_lo, ops.t_sum, ops.n_ks, false, nullptr,
+                      kHalves, t / pt, t % pt, lane);
+    }
+    stamp_end<kStamp>(stamp);
+}
+
 // kR: row tiles per workgroup.  kV: input elements per load (2 when input HCUs have an even number
 // of MCUs).  kS: row stride of the weight panel in LDS (panel_stride).
 // kMulti: several chunks (else the one chunk holds every active unit).  kFew: a single row, on
@@ -880,6 +903,13 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
     const int64_t row_tiles = (B + kRows - 1) / kRows;
     // the input rows of the last row tile (up to 15 past B) must have 32-bit byte offsets
     if (row_tiles * kRows * g.n_in * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    if (ops && target && !y && !s) {
+        const int64_t tasks = row_tiles * ((g.n_in + 63) / 64 + (g.n_out + 63) / 64);
+        if (row_tiles * kRows * g.n_out * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+        return launch_timed(stamp ? split_kernel<true> : split_kernel<false>,
+                            dim3((unsigned)((tasks + 3) / 4)), dim3(256), 0, stream, start, stop, g, x,
+                            B, target, *ops, input_sum_order(g, max_k), stamp);
+    }
     SupportLayout lay;
     size_t lds = 0;
     int shape = -1;

@@ -1,6 +1,6 @@
 """GPU: the support's launch shapes (one chunk, chunks, many rows, a single row) at the
 edges of their column tiles, unit chunks and input vectors, against the oracle's forward pass on a
-given state."""
+given state; and a supervised batch without activities, whose support is not computed."""
 import sys
 
 import numpy as np
@@ -69,3 +69,27 @@ def test_forward_and_readout_match_oracle(shape):
     best = s.reshape(B, hout, mout).argmax(2)    # the argmax of the GPU's own support: exact
     assert np.array_equal(win.cpu().numpy(), best)
     pair.close()
+
+
+@pytest.mark.parametrize("in_mcu,pairs,out_hcu,B", [(100, 0, 1, 37), (2, 1, 3, 130), (3, 0, 5, 16)])
+def test_supervised_batches_without_activities_leave_the_same_state(in_mcu, pairs, out_hcu, B):
+    """The traces take the target either way: the same bits."""
+    rng = np.random.default_rng(B)
+    hin, mout = 40, 10
+    p = rng.random((B, hin, in_mcu)) + 0.05
+    x = (p / p.sum(-1, keepdims=True)).reshape(B, -1).astype(np.float32)
+    if pairs:
+        x = synth.encode_pixels(rng.random((B, hin)).astype(np.float32))
+    target = np.tile(synth.one_hot(rng.integers(0, mout, B), mout), (1, out_hcu))
+    mask = np.stack([synth.random_mask(hin, 1, 25, c)[:, 0] for c in range(out_hcu)], 1)
+    states = []
+    for ask in (False, True):
+        pair = Pair(gpu_config(hin, in_mcu, out_hcu, mout, B, alpha=0.05, complement_pairs=pairs), mask)
+        t = pair.torch
+        y = t.empty((B, out_hcu * mout), device="cuda") if ask else None
+        for _ in range(3):
+            pair.gpu.train_batch(pair.dev(x), pair.dev(target), y)
+        states.append(pair.gpu.get_state())
+        pair.close()
+    for k, v in states[0].items():
+        assert np.array_equal(v, states[1][k]), k
