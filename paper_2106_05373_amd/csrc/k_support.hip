@@ -66,6 +66,8 @@ constexpr int kMaxWaves = 16;
 constexpr int64_t kManyRowTiles = 1024;
 constexpr int kCus = 256;                 // compute units
 constexpr int kMinSplit = 16;             // least workgroups for the input's split
+constexpr int kThinUnits = 512;           // active units from which a narrow layer goes row by row,
+constexpr int kThinRows = 1024;           // up to so many rows
 constexpr int kOneUnits = 1024;           // unit table of the one-chunk variants
 constexpr int kOneBytes = 120 * 1024;     // their panels and table
 constexpr int kManyTiles = 4;             // row tiles per workgroup of the many-rows variant
@@ -234,6 +236,99 @@ split_kernel(Geometry g, const float* __restrict__ x, int32_t B, const float* __
                       kHalves, t / pt, t % pt, lane);
     }
     stamp_end<kStamp>(stamp);
+}
+
+// A narrow hidden HCU with many active units and a small batch (a readout: 3000 units to 10
+// classes, 128 rows): by row tiles it would fill a handful of CUs, each with a long chain of
+// chunks.  Here a workgroup takes one row: a thread accumulates all M_out (<= 16) columns of its
+// units k, k + 512, ... with fp64 FMAs (W: floats per weight load), the waves add their lanes by
+// halving exchanges (after which lanes hold single columns), and 16 lanes add the waves in order,
+// then take the softmax or argmax.  Nothing waits between the loads and the reduction, and the
+// weights are read by every workgroup from L2.  Measured at 128 rows,
+// 3000 -> 10: 11 us (in chunks of units, 8 workgroups: 25 us; one column tile per wave: 87 us).
+constexpr int kThinThreads = 512;
+constexpr int kThinColumns = 16;
+template <int W>
+__global__ void __launch_bounds__(kThinThreads)
+support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __restrict__ w,
+                    const float* __restrict__ bias, const int32_t* __restrict__ act_list,
+                    const int32_t* __restrict__ act_count, uint32_t mcu_magic, float gain, int mode,
+                    float* __restrict__ y, float* __restrict__ s, int32_t* __restrict__ winner) {
+    typedef float wvec __attribute__((ext_vector_type(W)));
+    __shared__ double sums[kThinThreads / 64][kThinColumns];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hj = blockIdx.x % g.out_hcu;
+    const int row = blockIdx.x / g.out_hcu;
+    const int M = g.out_mcu;
+    const int32_t k_total = act_count[hj] * g.in_mcu;
+    const int32_t* alist = act_list + (int64_t)hj * g.in_hcu;
+    const float* wb = w + (int64_t)hj * M;
+    const float* xrow = x + (int64_t)row * g.n_in;
+    double acc[kThinColumns];
+#pragma unroll
+    for (int c = 0; c < kThinColumns; ++c) acc[c] = 0.0;
+    const bool full = k_total == g.n_in;                       // every input HCU active: unit k
+#pragma unroll 3
+    for (int32_t k = tid; k < k_total; k += kThinThreads) {
+        int32_t u = k;
+        if (!full) {
+            const int32_t h = mcu_magic ? (int32_t)__umulhi((uint32_t)k, mcu_magic) : k;
+            u = (alist[h] - h) * g.in_mcu + k;
+        }
+        const float* wr = wb + (int64_t)u * g.n_out;
+        wvec wv[kThinColumns / W];
+#pragma unroll
+        for (int q = 0; q < kThinColumns / W; ++q) {
+            wv[q] = wvec(0.0f);
+            if (W * q < M) wv[q] = *reinterpret_cast<const wvec*>(wr + W * q);
+        }
+        const double xv = (double)xrow[u];
+#pragma unroll
+        for (int q = 0; q < kThinColumns / W; ++q)
+            if (W * q < M) {
+#pragma unroll
+                for (int e = 0; e < W; ++e) acc[W * q + e] = fma(xv, (double)wv[q][e], acc[W * q + e]);
+            }
+    }
+    // halving exchanges: after the step of lane distance 32, 16, 8, 4 a lane holds 8, 4, 2, 1
+    // columns (the upper half where its lane bit is set); the last two steps add within quads
+#pragma unroll
+    for (int half = kThinColumns / 2, off = 32; half >= 1; half /= 2, off /= 2) {
+        const bool upper = (lane & off) != 0;
+#pragma unroll
+        for (int c = 0; c < half; ++c) {
+            const double send = upper ? acc[c] : acc[c + half];
+            const double keep = upper ? acc[c + half] : acc[c];
+            acc[c] = keep + __shfl_xor(send, off, 64);
+        }
+    }
+    acc[0] += __shfl_xor(acc[0], 2, 64);
+    acc[0] += __shfl_xor(acc[0], 1, 64);
+    if ((lane & 3) == 0) sums[wave][lane >> 2] = acc[0];       // lane bits 5..2 are the column's
+    lds_barrier();
+    if (tid >= kThinColumns) return;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kThinThreads / 64; ++q) v += sums[q][tid];
+    const bool in = tid < M;
+    const int64_t o = (int64_t)row * g.n_out + (int64_t)hj * M + tid;
+    const float sv = (float)(v + (double)bias[(int64_t)hj * M + (in ? tid : 0)]);
+    if (s && in) s[o] = sv;
+    if (mode == 0) {
+        const float mx = row16_max(in ? sv : -INFINITY);
+        const float e = in ? expf(gain * (sv - mx)) : 0.0f;
+        const float inv = 1.0f / row16_sum(e);
+        if (y && in) y[o] = e * inv;
+    } else {
+        float bv = in ? sv : -INFINITY;
+        int bi = in && sv > -INFINITY ? tid : 0x7fffffff;
+        for (int off = kThinColumns / 2; off > 0; off >>= 1) {
+            const float ov = __shfl_xor(bv, off, 64);
+            const int oi = __shfl_xor(bi, off, 64);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+        if (tid == 0) winner[(int64_t)row * g.out_hcu + hj] = bi;
+    }
 }
 
 // kR: row tiles per workgroup.  kV: input elements per load (2 when input HCUs have an even number
@@ -909,6 +1004,16 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
         return launch_timed(stamp ? split_kernel<true> : split_kernel<false>,
                             dim3((unsigned)((tasks + 3) / 4)), dim3(256), 0, stream, start, stop, g, x,
                             B, target, *ops, input_sum_order(g, max_k), stamp);
+    }
+    if (!ops && g.out_mcu <= kThinColumns && max_k >= kThinUnits &&
+        g.out_hcu == 1 && B <= kThinRows) {
+        const int width = g.out_mcu % 4 == 0 && g.n_out % 4 == 0 ? 4
+                          : g.out_mcu % 2 == 0 && g.n_out % 2 == 0 ? 2 : 1;
+        const uint32_t magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
+        return launch_timed(width == 4 ? support_thin_kernel<4>
+                            : width == 2 ? support_thin_kernel<2> : support_thin_kernel<1>,
+                            dim3((unsigned)(B * g.out_hcu)), dim3(kThinThreads), 0, stream, start, stop,
+                            g, x, w, bias, act_list, act_count, magic, gain, mode, y, s, winner);
     }
     SupportLayout lay;
     size_t lds = 0;

@@ -1,4 +1,4 @@
-"""GPU: the support's launch shapes (one chunk, chunks, many rows, a single row) at the
+"""GPU: the support's launch shapes (one chunk, chunks, many rows, a single row, row by row) at the
 edges of their column tiles, unit chunks and input vectors, against the oracle's forward pass on a
 given state; and a supervised batch without activities, whose support is not computed."""
 import sys
@@ -40,6 +40,8 @@ SHAPES = [
     (200, 2, 2, 129, 151, 17), (150, 3, 2, 257, 99, 16), (100, 2, 2, 513, 61, 18),
     # many rows: groups of four row tiles, the last one partial
     (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
+    # a readout, row by row: weight rows of 16, 8 and 4 bytes, ragged batches
+    (30, 100, 1, 16, 30, 40), (30, 100, 1, 10, 30, 128), (50, 13, 1, 7, 49, 19), (600, 1, 1, 2, 513, 1),
     # more active units than the larger stages leave room for in the unit table
     (6000, 2, 1, 40, 5900, 18), (12288, 1, 2, 20, 12288, 3),
 ]
