@@ -881,7 +881,9 @@ bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayo
     L.vec4 = g.out_mcu % 4 == 0 && g.n_out % 4 == 0;
     L.mpad = (g.out_mcu + 15) / 16 * 16 + 4;
     const int xv = input_vec(g);
-    const int waves = kR == 1 && !shape_one(v) ? kMaxWaves : 8;
+    // (2^22 workgroups of sixteen waves would be 2^32 work-items)
+    const int64_t n_main = ((int64_t)(B + kR * kRows - 1) / (kR * kRows)) * g.out_hcu;
+    const int waves = kR == 1 && !shape_one(v) && n_main < (1 << 22) - 2 * kCus ? kMaxWaves : 8;
     L.parts = waves / L.groups > 0 ? waves / L.groups : 1;
     // the chunk; the rows of the input panel lie 4 mod 8 words apart, so that the 16 rows x 4 units
     // of an operand read fall on different banks
@@ -917,7 +919,6 @@ bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayo
     L.n_row_tiles = (B + kRows - 1) / kRows;
     L.n_row_groups = (L.n_row_tiles + kR - 1) / kR;
     L.row_major = !shape_one(v);
-    const int64_t n_main = (int64_t)L.n_row_groups * g.out_hcu;
     if (n_main > INT32_MAX / 2) return false;
     L.n_main = (int)n_main;
     const size_t table = shape_one(v) ? 0 : (size_t)L.k_alloc * 4;
@@ -998,9 +999,9 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
     const int64_t row_tiles = (B + kRows - 1) / kRows;
     // the input rows of the last row tile (up to 15 past B) must have 32-bit byte offsets
     if (row_tiles * kRows * g.n_in * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    if (ops && target && !y && !s) {
+    // (the target's rows must have 32-bit byte offsets too)
+    if (ops && target && !y && !s && row_tiles * kRows * g.n_out * 4 <= (int64_t)UINT32_MAX) {
         const int64_t tasks = row_tiles * ((g.n_in + 63) / 64 + (g.n_out + 63) / 64);
-        if (row_tiles * kRows * g.n_out * 4 > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
         return launch_timed(stamp ? split_kernel<true> : split_kernel<false>,
                             dim3((unsigned)((tasks + 3) / 4)), dim3(256), 0, stream, start, stop, g, x,
                             B, target, *ops, input_sum_order(g, max_k), stamp);
