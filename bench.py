@@ -23,7 +23,7 @@ caller's stream, which carries the schedule: the support, the active-block trace
 where it runs on that stream, the sweep over the silent elements of Pij, per batch of its
 launch), the sweep against the HBM roofline and the support against the fp64 matrix cores
 (both reported, whichever dominates), the caller's stream per batch, and the structural update.  The line also
-carries the whole-matrix weight pass, the STL-shaped layer (a short run of the same schedule on
+carries the log-weight pass, the STL-shaped layer (a short run of the same schedule on
 the first images of that workload, with its weight pass), the forward-pass throughput by batch
 size, and the CPU oracle on a bounded sample of the MNIST-shaped schedule on this host's cores
 (all threads, and one).
@@ -54,7 +54,7 @@ SWEEP_BATCHES = 8
 # is timed.
 PROFILE_PERIOD = 1
 PROFILE_SYNC = 64             # steps of the profiling pass between two reads of the timers
-# Launches of the whole-matrix weight pass timed after the training run.
+# Launches of the log-weight pass timed after the training run.
 WEIGHT_PASSES = 20
 # Structural updates timed after the profiling pass.
 STRUCTURAL_TIMED = 3
@@ -354,7 +354,7 @@ def measure_training(w, warmup, steps, pairs, profile_steps=None, n_images=None,
     for _ in range(STRUCTURAL_TIMED):
         layer.structural_update(count=False)
     su_ms, su_n = layer.profile_read_kernel("structural")
-    # the whole-matrix log-weight pass (recompute_weights), timed the same way
+    # the log-weight pass (recompute_weights), timed the same way
     for _ in range(WEIGHT_PASSES):
         layer.recompute_weights()
     wp_ms, wp_n = layer.profile_read_kernel("weights")
@@ -491,14 +491,14 @@ def measure_training(w, warmup, steps, pairs, profile_steps=None, n_images=None,
         "in_timed_region": plastic_steps,
     }
 
-    # ---- the log-weight pass over the whole matrix (recompute_weights) ----------------------
-    # Per launch it writes every w and reads the Pij of active blocks (a silent weight is 0
-    # whatever its trace), plus Pi, Pj and the mask.
-    wp_bytes = 4.0 * E + 4.0 * active + 4.0 * (L.n_in + L.n_out) + L.in_hcu * L.out_hcu
+    # ---- the log-weight pass (recompute_weights) ---------------------------------------------
+    # Per launch it reads Pij and writes w in the active blocks (a silent weight is 0 whatever its
+    # trace, and holds it already), plus Pi, Pj, b and the active lists.
+    wp_bytes = 8.0 * active + 4.0 * (L.n_in + 2 * L.n_out) + 4.0 * active / L.out_mcu / L.in_mcu
     wp_s = wp_ms / 1e3 / max(wp_n, 1)
     weight_pass = {
-        "kernel": "recompute_weights_vec_kernel (w = mask ? log(Pij / (Pi Pj)) : 0 over the "
-                  "whole matrix, Pij read for active blocks only)",
+        "kernel": "recompute_active_kernel (w = log(Pij / (Pi Pj)) on the active blocks; the "
+                  "silent ones hold 0)",
         "bound": "hbm", "achieved": round(wp_bytes / wp_s / 1e9, 1) if wp_n else None,
         "peak": PEAK_HBM_GBS, "unit": "GB/s",
         "frac": round(wp_bytes / wp_s / 1e9 / PEAK_HBM_GBS, 4) if wp_n else None,

@@ -229,7 +229,7 @@ bcpnn_status bcpnn_profile_read(bcpnn_layer *layer, double *total_ms, int32_t *l
 
 /* The same for one kernel: the silent-block sweep, the support (with softmax and the
  * contraction operands) or the active-block trace kernel of train_batch, the weight pass of
- * recompute_weights (w over the whole matrix; the bias kernel after it is not included), or
+ * recompute_weights (w of the active blocks, and b), or
  * the structural update (from the start of the mutual-information kernel to the end of the
  * swap kernel; the queued sweep it applies first is not included).  The support and active
  * kernels, short launches on the caller's stream, are not bracketed by events: a timed launch

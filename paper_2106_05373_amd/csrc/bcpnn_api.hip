@@ -642,9 +642,9 @@ bcpnn_status bcpnn_recompute_weights(bcpnn_layer* L) {
     HIP_TRY(L, join_side(L));
     hipEvent_t t0, t1;
     HIP_TRY(L, timer_events(L, BCPNN_KERNEL_WEIGHTS, &t0, &t1));
-    HIP_TRY(L, bcpnn::launch_recompute_weights(L->stream, L->g, L->mask, L->pi[L->cur],
-                                               L->pj[L->cur], L->pij, L->cfg.eps,
-                                               L->cfg.bias_gain, L->drop_bits, L->w, L->b,
+    HIP_TRY(L, bcpnn::launch_recompute_weights(L->stream, L->g, L->act_list, L->act_count,
+                                               L->max_active, L->pi[L->cur], L->pj[L->cur], L->pij,
+                                               L->cfg.eps, L->cfg.bias_gain, L->drop_bits, L->w, L->b,
                                                t0, t1));
     return BCPNN_OK;
 }

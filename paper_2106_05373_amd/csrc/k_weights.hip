@@ -1,14 +1,16 @@
-// Whole-matrix sweeps over Pij / w: initial state, weight recompute, mask application.
+// Initial state, weight recompute, mask application.
 //
-// These are bandwidth-bound passes (one read and/or one write of 4 bytes per element).  Each
-// workgroup takes one row i of the [N_in][N_out] matrices per iteration of a grid-stride loop
-// over rows; within a row the lanes walk consecutive columns, so every wave touches
-// contiguous spans.  The mask row [out_hcu] of the row's input HCU is read through the cache.
+// Initial state and mask application are whole-matrix passes: each workgroup takes one row i of the
+// [N_in][N_out] matrices per iteration of a grid-stride loop over rows; within a row the lanes walk
+// consecutive columns, so every wave touches contiguous spans.  The mask row [out_hcu] of the row's
+// input HCU is read through the cache.
 //
-// The weight recompute (Alg. 1 weight and mask lines) writes every w but reads Pij only where
-// the mask is set: a silent weight is 0 whatever its trace.  When N_out is a multiple of 4
-// (16-byte rows) each lane moves 16 bytes per access, eight accesses in flight, finds a column's
-// hidden HCU by a multiply-high instead of a division, and stores w with the non-temporal hint.
+// The weight recompute (Alg. 1 weight and mask lines) touches the active blocks only.  A silent
+// weight is 0, and every writer of w keeps it so: the initial state, the upload (apply_mask_kernel),
+// the structural update (which zeroes what it silences) and the batches (which write active blocks).
+// Rewriting those zeros was 95% of the pass on the STL-shaped layer: with its reads coming from HBM
+// between the stores, 690 us (2.3 GB, 3.4 TB/s; 390 us when the reads are repeated and stay in the
+// Infinity Cache), against 54 us for the 221 MB of the active blocks.
 #include "bcpnn_internal.h"
 #include "device_common.h"
 
@@ -37,91 +39,55 @@ init_state_kernel(Geometry g, const uint8_t* __restrict__ mask, float pij0, floa
     }
 }
 
+// w of one hidden HCU's active units, V floats per lane: `lanes` (a power of two, at most 64) lanes
+// take a unit's row segment, kWeightRows rows per lane in flight.  Workgroups past n_work store the
+// bias.  (A row per 32 lanes leaves 7 of 32 idle at 100 MCUs; the pass waits for memory, not lanes.)
+constexpr int kWeightRows = 4;
+template <int V>
 __global__ void __launch_bounds__(kSweepThreads)
-recompute_weights_kernel(Geometry g, const uint8_t* __restrict__ mask,
-                         const float* __restrict__ pi, const float* __restrict__ pj,
-                         const float* __restrict__ pij, float eps, int drop,
-                         float* __restrict__ w) {
-    for (int64_t i = blockIdx.x; i < g.n_in; i += gridDim.x) {
-        const uint8_t* mrow = mask + (int64_t)(i / g.in_mcu) * g.out_hcu;
-        const float pii = pi[i];
-        const float* prow = pij + i * g.n_out;
-        float* wrow = w + i * g.n_out;
-        for (int64_t j = threadIdx.x; j < g.n_out; j += kSweepThreads) {
-            float v = 0.0f;
-            if (mrow[j / g.out_mcu]) v = log_ratio(prow[j], pii, pj[j], eps);
-            wrow[j] = round_storage(v, drop);
+recompute_active_kernel(Geometry g, const int32_t* __restrict__ act_list,
+                        const int32_t* __restrict__ act_count, uint32_t per_hcu, uint32_t n_work,
+                        uint32_t n_bias, int lanes, uint32_t mcu_magic, const float* __restrict__ pi,
+                        const float* __restrict__ pj, const float* __restrict__ pij, float eps,
+                        float bias_gain, int drop, float* __restrict__ w, float* __restrict__ b) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    for (uint32_t work = blockIdx.x; work < n_work + n_bias; work += gridDim.x) {
+        if (work >= n_work) {
+            const int64_t j = (int64_t)(work - n_work) * kSweepThreads + threadIdx.x;
+            if (j < g.n_out) b[j] = bias_gain * __logf(fmaxf(pj[j], eps));
+            continue;
         }
-    }
-}
-
-constexpr int kWeightUnroll = 8;    // 16-byte accesses per lane in flight
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Streaming store: w is not read again by this pass, so it need not stay in the caches.
-__device__ __forceinline__ void store_streaming(float4* p, float4 v) {
-    const f32x4 x = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(x, reinterpret_cast<f32x4*>(p));
-}
-
-// Hidden HCU of column j: floor(j / out_mcu) as the high word of j * ceil(2^32 / out_mcu),
-// exact for out_mcu >= 2 while j * out_mcu < 2^32 (both checked by the launcher).
-__device__ __forceinline__ uint32_t column_hcu(uint32_t j, uint32_t magic) {
-    return __umulhi(j, magic);
-}
-
-__device__ __forceinline__ float weight_of(bool live, float pij, float pi, float pj, float eps,
-                                           int drop) {
-    return live ? round_storage(log_ratio(pij, pi, pj, eps), drop) : 0.0f;
-}
-
-__global__ void __launch_bounds__(kSweepThreads)
-recompute_weights_vec_kernel(Geometry g, const uint8_t* __restrict__ mask,
-                             const float* __restrict__ pi, const float* __restrict__ pj,
-                             const float* __restrict__ pij, float eps, int drop, uint32_t magic,
-                             float* __restrict__ w) {
-    const uint32_t n4 = (uint32_t)(g.n_out >> 2);
-    const float4* pj4 = reinterpret_cast<const float4*>(pj);
-    for (int64_t i = blockIdx.x; i < g.n_in; i += gridDim.x) {
-        const uint8_t* mrow = mask + (int64_t)(i / g.in_mcu) * g.out_hcu;
-        const float pii = pi[i];
-        const float4* prow = reinterpret_cast<const float4*>(pij + i * g.n_out);
-        float4* wrow = reinterpret_cast<float4*>(w + i * g.n_out);
-        for (uint32_t q0 = threadIdx.x; q0 < n4; q0 += kSweepThreads * kWeightUnroll) {
-            float4 p[kWeightUnroll], pq[kWeightUnroll];
-            uint32_t live[kWeightUnroll];     // bit e: column 4q + e is in an active block
+        const int hj = work / per_hcu;
+        const int rows_at_once = kSweepThreads / lanes;
+        const int r0 = (work % per_hcu) * rows_at_once * kWeightRows + threadIdx.x / lanes;
+        const int c0 = V * (threadIdx.x & (lanes - 1));
+        const int k_total = act_count[hj] * g.in_mcu;
+        if (r0 >= k_total) continue;
+        const int32_t* list = act_list + (int64_t)hj * g.in_hcu;
+        const int64_t col0 = (int64_t)hj * g.out_mcu;
+        int64_t row[kWeightRows];
+        float pr[kWeightRows];
 #pragma unroll
-            for (int u = 0; u < kWeightUnroll; ++u) {
-                const uint32_t q = q0 + u * kSweepThreads;
-                live[u] = 0;
-                p[u] = pq[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (q < n4) {
-                    const uint32_t j = 4 * q;
-                    const uint32_t h0 = column_hcu(j, magic), h3 = column_hcu(j + 3, magic);
-                    const uint32_t m0 = mrow[h0] != 0, m3 = mrow[h3] != 0;
+        for (int q = 0; q < kWeightRows; ++q) {
+            const int k = r0 + rows_at_once * q;
+            const int kk = k < k_total ? k : 0;
+            const int h = mcu_magic ? (int)__umulhi((uint32_t)kk, mcu_magic) : kk;
+            const int64_t i = (int64_t)list[h] * g.in_mcu + (kk - h * g.in_mcu);
+            pr[q] = pi[i];
+            row[q] = i * g.n_out + col0;
+        }
+        for (int c = c0; c < g.out_mcu; c += V * lanes) {
+            const vec pc = *reinterpret_cast<const vec*>(pj + col0 + c);
+            vec p[kWeightRows];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t h = column_hcu(j + e, magic);
-                        const uint32_t m = h == h0 ? m0 : h == h3 ? m3 : (mrow[h] != 0);
-                        live[u] |= m << e;
-                    }
-                    if (live[u]) {
-                        p[u] = prow[q];
-                        pq[u] = pj4[q];
-                    }
-                }
-            }
+            for (int q = 0; q < kWeightRows; ++q) p[q] = *reinterpret_cast<const vec*>(pij + row[q] + c);
 #pragma unroll
-            for (int u = 0; u < kWeightUnroll; ++u) {
-                const uint32_t q = q0 + u * kSweepThreads;
-                if (q >= n4) continue;
-                float4 v;
-                v.x = weight_of(live[u] & 1u, p[u].x, pii, pq[u].x, eps, drop);
-                v.y = weight_of(live[u] & 2u, p[u].y, pii, pq[u].y, eps, drop);
-                v.z = weight_of(live[u] & 4u, p[u].z, pii, pq[u].z, eps, drop);
-                v.w = weight_of(live[u] & 8u, p[u].w, pii, pq[u].w, eps, drop);
-                store_streaming(&wrow[q], v);
+            for (int q = 0; q < kWeightRows; ++q) {
+                if (r0 + rows_at_once * q >= k_total) continue;
+                vec v;
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = round_storage(log_ratio(p[q][e], pr[q], pc[e], eps), drop);
+                *reinterpret_cast<vec*>(w + row[q] + c) = v;
             }
         }
     }
@@ -159,30 +125,29 @@ hipError_t launch_init_state(hipStream_t stream, const Geometry& g, const uint8_
     return hipGetLastError();
 }
 
-hipError_t launch_recompute_weights(hipStream_t stream, const Geometry& g, const uint8_t* mask,
-                                    const float* pi, const float* pj, const float* pij,
-                                    float eps, float bias_gain, int drop_bits, float* w,
-                                    float* b, hipEvent_t start, hipEvent_t stop) {
-    // 16-byte rows and an exact multiply-high HCU lookup (out_mcu >= 2, so that the multiplier
-    // fits 32 bits): the vector kernel; else the scalar one
-    hipError_t e;
-    if (g.n_out % 4 == 0 && g.out_mcu >= 2 &&
-        (uint64_t)g.n_out * (uint64_t)g.out_mcu < (1ull << 32)) {
-        const uint32_t magic =
-            (uint32_t)(((1ull << 32) + (uint64_t)g.out_mcu - 1) / (uint64_t)g.out_mcu);
-        // one row per workgroup: short-lived workgroups keep the stores streaming (a
-        // grid-stride loop over rows with fewer workgroups writes at about 5.5 against 6.3 TB/s)
-        const int64_t rows = g.n_in < (int64_t)1 << 30 ? g.n_in : (int64_t)1 << 30;
-        e = launch_timed(recompute_weights_vec_kernel, dim3((unsigned)rows),
-                         dim3(kSweepThreads), 0, stream, start, stop, g, mask, pi, pj,
-                         pij, eps, drop_bits, magic, w);
-    } else {
-        e = launch_timed(recompute_weights_kernel, dim3(sweep_blocks(g)),
-                         dim3(kSweepThreads), 0, stream, start, stop, g, mask, pi, pj,
-                         pij, eps, drop_bits, w);
-    }
-    if (e != hipSuccess) return e;
-    return launch_bias(stream, g, pj, eps, bias_gain, b);
+hipError_t launch_recompute_weights(hipStream_t stream, const Geometry& g, const int32_t* act_list,
+                                    const int32_t* act_count, int32_t max_active, const float* pi,
+                                    const float* pj, const float* pij, float eps, float bias_gain,
+                                    int drop_bits, float* w, float* b, hipEvent_t start,
+                                    hipEvent_t stop) {
+    // 16 bytes per lane where every row segment is 16-byte aligned
+    const int V = g.out_mcu % 4 == 0 && g.n_out % 4 == 0 ? 4 : 1;
+    int lanes = 1;
+    while (lanes < 64 && lanes * V < g.out_mcu) lanes *= 2;
+    const int64_t rows = (int64_t)(kSweepThreads / lanes) * kWeightRows;
+    const int64_t per_hcu = ((int64_t)max_active * g.in_mcu + rows - 1) / rows;
+    const int64_t n_work = per_hcu * g.out_hcu;
+    const int64_t n_bias = (g.n_out + kSweepThreads - 1) / kSweepThreads;
+    if (n_work + n_bias >= (1ll << 31)) return hipErrorInvalidValue;
+    const int64_t cap = 1 << 22;                        // (a launch holds less than 2^32 work-items)
+    const int64_t blocks = n_work + n_bias < cap ? n_work + n_bias : cap;
+    const uint32_t magic = g.in_mcu > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)g.in_mcu - 1) /
+                                                     (uint64_t)g.in_mcu)
+                                        : 0;
+    return launch_timed(V == 4 ? recompute_active_kernel<4> : recompute_active_kernel<1>,
+                        dim3((unsigned)blocks), dim3(kSweepThreads), 0, stream, start, stop, g,
+                        act_list, act_count, (uint32_t)per_hcu, (uint32_t)n_work, (uint32_t)n_bias,
+                        lanes, magic, pi, pj, pij, eps, bias_gain, drop_bits, w, b);
 }
 
 hipError_t launch_bias(hipStream_t stream, const Geometry& g, const float* pj, float eps,
