@@ -19,6 +19,7 @@ namespace bcpnn {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kSwapThreads = 1024;
 constexpr int kMaxSwaps = 256;
 
 // kGroup lanes per block, 64 / kGroup blocks per wave (consecutive blocks: neighbouring hidden
@@ -27,55 +28,89 @@ constexpr int kMaxSwaps = 256;
 // issued together), each chunk row by row; an xor butterfly over the group then adds the
 // partial sums, leaving the same bits in every lane of the group.  The pattern depends only on
 // positions inside the block.  Few lanes per block keep the lanes busy with fp64 log terms
-// (M_out = 100: 13 columns per lane for 8 lanes) rather than with per-block reductions; the log
-// is log_positive (fp64_log.h), a third of the instructions of the general library log.
+// (M_out = 100: 13 columns per lane for 8 lanes) rather than with per-block reductions.
+//
+// The kernel is bound by fp64 instructions, so a term holds no division: the quotient
+// Pij / (Pi Pj) comes from the reciprocals of Pi (one per row) and Pj (one per column), corrected
+// by its residual to within a rounding of the division; the log takes a table (log_by_table).
+// STL-shaped layer (553 M terms): 0.99 ms, with a division and a log by division per term 1.47.
+// Without the log it takes 0.60, without the loads of Pij 0.80.  Two columns at a time: 8 to 10%
+// less than three, four or six (more registers, fewer waves) and 30% less than one; the columns
+// past the last full chunk go one by one, since an empty slot costs as much as a term.  The grid is
+// capped because each workgroup fills its table first.
 constexpr int kGroup = 8;
-constexpr int kColChunk = 4;
+constexpr int kColChunk = 2;
+constexpr int64_t kMiBlocks = 16384;
+__constant__ const LogTable kLogTable = log_table();
+
+// 1 / x to about two ulp: the hardware's estimate and two Newton steps.
+__device__ __forceinline__ double reciprocal(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// The terms of kN columns (kGroup apart, all inside the block) and every row of a block; pj and
+// pij point at the first column.
+template <int kN>
+__device__ __forceinline__ double mi_columns(int in_mcu, int64_t n_out, const float* __restrict__ pi,
+                                             const float* __restrict__ pj,
+                                             const float* __restrict__ pij, double e,
+                                             const LogCell* cells, double part) {
+    double pjc[kN], rj[kN];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) {
+        pjc[k] = fmax((double)pj[k * kGroup], e);
+        rj[k] = reciprocal(pjc[k]);
+    }
+    for (int m = 0; m < in_mcu; ++m) {
+        float q[kN];
+#pragma unroll
+        for (int k = 0; k < kN; ++k) q[k] = pij[m * n_out + k * kGroup];
+        const double pim = fmax((double)pi[m], e);
+        const double ri = reciprocal(pim);
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            const double v = fmax((double)q[k], e), den = pim * pjc[k], r = ri * rj[k];
+            const double x0 = v * r;
+            const double x = fma(fma(-den, x0, v), r, x0);
+            part = fma((double)q[k], log_by_table(x, cells), part);   // (0 log = 0)
+        }
+    }
+    return part;
+}
 
 __global__ void __launch_bounds__(kThreads)
 mi_kernel(Geometry g, const float* __restrict__ pi, const float* __restrict__ pj,
           const float* __restrict__ pij, float eps, double* __restrict__ mi) {
+    __shared__ LogCell cells[kLogCells];
+    for (int q = threadIdx.x; q < kLogCells; q += kThreads) cells[q] = kLogTable.cell[q];
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int sub = lane % kGroup;
     const int64_t n_blk = (int64_t)g.in_hcu * g.out_hcu;
-    const int64_t blk = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) *
-                            (64 / kGroup) + lane / kGroup;
-    if (((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * (64 / kGroup) >= n_blk)
-        return;                                                   // whole wave
-    const bool live = blk < n_blk;
-    const int64_t b = live ? blk : n_blk - 1;                     // clamped lanes still reduce
-    const int64_t hi = b / g.out_hcu;
-    const int64_t hj = b - hi * g.out_hcu;
+    const int64_t step = (int64_t)gridDim.x * (kThreads / 64) * (64 / kGroup);
     const double e = (double)eps;
-    double part = 0.0;
-    for (int c0 = sub; c0 < g.out_mcu; c0 += kGroup * kColChunk) {
-        double pjc[kColChunk];
+    for (int64_t first = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * (64 / kGroup);
+         first < n_blk; first += step) {
+        const int64_t blk = first + lane / kGroup;
+        const bool live = blk < n_blk;
+        const int64_t b = live ? blk : n_blk - 1;                 // clamped lanes still reduce
+        const int64_t hi = b / g.out_hcu;
+        const int64_t hj = b - hi * g.out_hcu;
+        const float* pi_b = pi + hi * g.in_mcu;
+        const float* pj_b = pj + hj * g.out_mcu;
+        const float* pij_b = pij + hi * g.in_mcu * g.n_out + hj * g.out_mcu;
+        double part = 0.0;
+        int c = sub;
+        for (; c + (kColChunk - 1) * kGroup < g.out_mcu; c += kGroup * kColChunk)
+            part = mi_columns<kColChunk>(g.in_mcu, g.n_out, pi_b, pj_b + c, pij_b + c, e, cells, part);
+        for (; c < g.out_mcu; c += kGroup)
+            part = mi_columns<1>(g.in_mcu, g.n_out, pi_b, pj_b + c, pij_b + c, e, cells, part);
 #pragma unroll
-        for (int k = 0; k < kColChunk; ++k) {
-            const int c = c0 + k * kGroup;
-            pjc[k] = c < g.out_mcu ? fmax((double)pj[hj * g.out_mcu + c], e) : 1.0;
-        }
-        for (int m = 0; m < g.in_mcu; ++m) {
-            const int64_t i = hi * g.in_mcu + m;
-            const double pim = fmax((double)pi[i], e);
-            float q[kColChunk];
-#pragma unroll
-            for (int k = 0; k < kColChunk; ++k) {
-                const int c = c0 + k * kGroup;
-                q[k] = c < g.out_mcu ? pij[i * g.n_out + hj * g.out_mcu + c] : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < kColChunk; ++k) {
-                if (q[k] != 0.0f) {
-                    const double den = pim * pjc[k];
-                    part += (double)q[k] * log_positive(fmax((double)q[k], e) / den);
-                }
-            }
-        }
+        for (int off = kGroup / 2; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
+        if (live && sub == 0) mi[blk] = part;
     }
-#pragma unroll
-    for (int off = kGroup / 2; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
-    if (live && sub == 0) mi[blk] = part;
 }
 
 struct Pick {
@@ -92,32 +127,34 @@ __device__ __forceinline__ bool better_high(double v, int32_t i, const Pick& p) 
     return v > p.v || (v == p.v && i < p.i);
 }
 
-// One workgroup per hidden HCU.  The HCU's mask column lives in LDS while it is edited:
-// 1 = active, 0 = silent, 2 = silenced now, 3 = activated now (2 and 3 are excluded from the
-// later swaps of this update).
-__global__ void __launch_bounds__(kThreads)
+// One workgroup per hidden HCU, a chain of strided reads of its score and mask columns: sixteen
+// waves, so that few of them follow one another (STL-shaped layer, 100 hidden HCUs: 81 us, with
+// four waves 111).  The HCU's mask column lives in LDS while it is edited: 1 = active, 0 = silent,
+// 2 = silenced now, 3 = activated now (2 and 3 are excluded from the later swaps of this update).
+template <int kT>
+__global__ void __launch_bounds__(kT)
 swap_kernel(Geometry g, const double* __restrict__ mi, int32_t n_swaps,
             const float* __restrict__ pi, const float* __restrict__ pj,
             const float* __restrict__ pij, float eps, int drop, uint8_t* __restrict__ mask,
             float* __restrict__ w, int32_t* __restrict__ act_list,
             int32_t* __restrict__ act_count, int32_t* __restrict__ swap_count) {
     extern __shared__ uint8_t mcol[];                 // [in_hcu]
-    __shared__ Pick red_lo[kThreads / 64], red_hi[kThreads / 64];
+    __shared__ Pick red_lo[kT / 64], red_hi[kT / 64];
     __shared__ int32_t sw_a[kMaxSwaps], sw_s[kMaxSwaps];
     __shared__ int32_t n_done, stop;
-    __shared__ int32_t scan[kThreads];
+    __shared__ int32_t scan[kT / 64];
 
     const int hj = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t hin = g.in_hcu;
 
-    for (int32_t h = tid; h < hin; h += kThreads) mcol[h] = mask[(int64_t)h * g.out_hcu + hj];
+    for (int32_t h = tid; h < hin; h += kT) mcol[h] = mask[(int64_t)h * g.out_hcu + hj];
     if (tid == 0) n_done = 0;
     __syncthreads();
 
     for (int32_t t = 0; t < n_swaps; ++t) {
         Pick lo{INFINITY, INT_MAX}, hi{-INFINITY, INT_MAX};
-        for (int32_t h = tid; h < hin; h += kThreads) {
+        for (int32_t h = tid; h < hin; h += kT) {
             const uint8_t m = mcol[h];
             const double v = mi[(int64_t)h * g.out_hcu + hj];
             if (m == 1 && better_low(v, h, lo)) lo = Pick{v, h};
@@ -138,7 +175,7 @@ swap_kernel(Geometry g, const double* __restrict__ mi, int32_t n_swaps,
         __syncthreads();
         if (tid == 0) {
             Pick L = red_lo[0], H = red_hi[0];
-            for (int q = 1; q < kThreads / 64; ++q) {
+            for (int q = 1; q < kT / 64; ++q) {
                 if (better_low(red_lo[q].v, red_lo[q].i, L)) L = red_lo[q];
                 if (better_high(red_hi[q].v, red_hi[q].i, H)) H = red_hi[q];
             }
@@ -157,7 +194,7 @@ swap_kernel(Geometry g, const double* __restrict__ mi, int32_t n_swaps,
     }
 
     const int32_t done = n_done;
-    for (int32_t q = tid; q < done; q += kThreads) {
+    for (int32_t q = tid; q < done; q += kT) {
         mcol[sw_a[q]] = 0;
         mcol[sw_s[q]] = 1;
         mask[(int64_t)sw_a[q] * g.out_hcu + hj] = 0;
@@ -169,7 +206,7 @@ swap_kernel(Geometry g, const double* __restrict__ mi, int32_t n_swaps,
     for (int32_t q = 0; q < done; ++q) {
         for (int side = 0; side < 2; ++side) {
             const int64_t h = side ? sw_s[q] : sw_a[q];
-            for (int32_t e = tid; e < blk_elems; e += kThreads) {
+            for (int32_t e = tid; e < blk_elems; e += kT) {
                 const int64_t i = h * g.in_mcu + e / g.out_mcu;
                 const int64_t j = (int64_t)hj * g.out_mcu + e % g.out_mcu;
                 const int64_t idx = i * g.n_out + j;
@@ -181,25 +218,24 @@ swap_kernel(Geometry g, const double* __restrict__ mi, int32_t n_swaps,
 
     // Rebuild the ascending list of active input HCUs: each thread counts a contiguous range,
     // an exclusive scan over the threads gives the output offsets.
-    const int32_t per = (hin + kThreads - 1) / kThreads;
+    const int32_t per = (hin + kT - 1) / kT;
     const int32_t lo_h = tid * per;
     const int32_t hi_h = lo_h + per < hin ? lo_h + per : hin;
     int32_t cnt = 0;
     for (int32_t h = lo_h; h < hi_h; ++h) cnt += mcol[h] == 1;
-    scan[tid] = cnt;
+    int32_t upto = cnt;                                // inclusive over the wave
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t v = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += v;
+    }
+    if (lane == 63) scan[wave] = upto;
     __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int q = 0; q < kThreads; ++q) {
-            const int32_t c = scan[q];
-            scan[q] = run;
-            run += c;
-        }
-        act_count[hj] = run;
+    int32_t pos = upto - cnt;
+    for (int q = 0; q < wave; ++q) pos += scan[q];
+    if (tid == kT - 1) {
+        act_count[hj] = pos + cnt;
         swap_count[hj] = done;
     }
-    __syncthreads();
-    int32_t pos = scan[tid];
     int32_t* list = act_list + (int64_t)hj * hin;
     for (int32_t h = lo_h; h < hi_h; ++h)
         if (mcol[h] == 1) list[pos++] = h;
@@ -233,7 +269,8 @@ hipError_t launch_mutual_information(hipStream_t stream, const Geometry& g, cons
                                      const float* pj, const float* pij, float eps, double* mi,
                                      hipEvent_t start) {
     const int64_t per_wg = (int64_t)(kThreads / 64) * (64 / kGroup);
-    const int64_t blocks = ((int64_t)g.in_hcu * g.out_hcu + per_wg - 1) / per_wg;
+    int64_t blocks = ((int64_t)g.in_hcu * g.out_hcu + per_wg - 1) / per_wg;
+    if (blocks > kMiBlocks) blocks = kMiBlocks;      // each fills its log table once
     return launch_timed(mi_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, start,
                         nullptr, g, pi, pj, pij, eps, mi);
 }
@@ -244,7 +281,10 @@ hipError_t launch_plasticity_swap(hipStream_t stream, const Geometry& g, const d
                                   float* w, int32_t* act_list, int32_t* act_count,
                                   int32_t* swap_count, hipEvent_t stop) {
     if (n_swaps > kMaxSwaps) return hipErrorInvalidValue;
-    return launch_timed(swap_kernel, dim3((unsigned)g.out_hcu), dim3(kThreads),
+    // (2^22 workgroups of 1024 threads would be 2^32 work-items)
+    const bool wide = g.out_hcu < 1 << 22;
+    return launch_timed(wide ? swap_kernel<kSwapThreads> : swap_kernel<kThreads>,
+                        dim3((unsigned)g.out_hcu), dim3(wide ? kSwapThreads : kThreads),
                         (size_t)g.in_hcu, stream, nullptr, stop, g, mi, n_swaps, pi, pj,
                         pij, eps, drop_bits, mask, w, act_list, act_count, swap_count);
 }
