@@ -118,19 +118,19 @@ def default_config(in_hcu, in_mcu, out_hcu, out_mcu, max_batch, **overrides) -> 
 
 
 def _dev_ptr(t, name, dtype=None, shape=None):
-    """Data pointer of a contiguous CUDA tensor (checked), or None."""
+    """Data pointer of a contiguous CUDA tensor (checked), or None.  The small layers' batches are
+    bound by the host, so the checks build no objects."""
     if t is None:
         return None
-    import torch
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _host(a: np.ndarray, dtype, shape):
@@ -181,14 +181,12 @@ class Layer:
 
     # -- compute ---------------------------------------------------------------------------
     def forward(self, x, y, s=None):
-        import torch
         B = x.shape[0]
         _check(lib.bcpnn_forward(self._h, _dev_ptr(x, "x", torch.float32, (B, self.n_in)), B,
                                  _dev_ptr(y, "y", torch.float32, (B, self.n_out)),
                                  _dev_ptr(s, "s", torch.float32, (B, self.n_out))))
 
     def train_batch(self, x, target=None, y=None):
-        import torch
         B = x.shape[0]
         _check(lib.bcpnn_train_batch(self._h, _dev_ptr(x, "x", torch.float32, (B, self.n_in)), B,
                                      _dev_ptr(target, "target", torch.float32, (B, self.n_out)),
@@ -213,7 +211,6 @@ class Layer:
             self._h, _dev_ptr(n_swapped, "n_swapped", torch.int32, (1,))))
 
     def readout(self, x, winner):
-        import torch
         B = x.shape[0]
         _check(lib.bcpnn_readout(self._h, _dev_ptr(x, "x", torch.float32, (B, self.n_in)), B,
                                  _dev_ptr(winner, "winner", torch.int32, (B, self.cfg.out_hcu))))
