@@ -1280,9 +1280,14 @@ trace_sweep_pair_tile_sum_kernel(Geometry g, SweepArgs a, int n_tj) {
 // work): a workgroup covers two column blocks, and each block's contraction is run by two
 // waves, one storing the first rows of the pairs and one the second, so that every wave keeps
 // the per-element work of the unpaired kernel.  Otherwise a workgroup covers four column blocks
-// and each wave stores both rows.
+// and each wave stores both rows; such a layer has many workgroups in turn, each a chain of memory
+// round trips, so the kernel is kept to 128 registers and four waves per SIMD: the x operands are
+// read from LDS at their products, and the old traces and marginals requested after them.
+// STL-shaped layer, batch of 256: 226 us (two waves per SIMD, everything requested first: 262).
+// Chunks of four k-steps, at 117 registers, or three waves with the early requests: the same.
 template <int kDropBits, bool kSplit, bool kStamp>
-__global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(kWaves * 64)
+__attribute__((amdgpu_waves_per_eu(kSplit ? 2 : 4, kSplit ? 2 : 4)))
 trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ act_list,
                          const int32_t* __restrict__ act_count, int n_rt, int n_cgr,
                          int n_work) {
@@ -1318,7 +1323,7 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
     const int k_total = act_count[hj];
     const int kr = rt * 32 + jl < g.in_hcu ? rt * 32 + jl : g.in_hcu - 1;
     const int hsel = act_list[(int64_t)hj * g.in_hcu + kr];
-    u32x4 opt[kActiveChunk][2], opx[kActiveChunk][2];
+    u32x4 opt[kActiveChunk][2], opx[kSplit ? kActiveChunk : 1][2];
     auto load_t = [&](int k0) {
 #pragma unroll
         for (int c = 0; c < kActiveChunk; ++c) {
@@ -1345,10 +1350,12 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
         }
     };
     auto load_x = [&]() {
+        if constexpr (kSplit) {
 #pragma unroll
-        for (int c = 0; c < kActiveChunk; ++c) {
-            opx[c][0] = xs[c][0][lane];
-            opx[c][1] = xs[c][1][lane];
+            for (int c = 0; c < kActiveChunk; ++c) {
+                opx[c][0] = xs[c][0][lane];
+                opx[c][1] = xs[c][1][lane];
+            }
         }
     };
     f16v acc = {};
@@ -1356,8 +1363,10 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
 #pragma unroll
         for (int c = 0; c < kActiveChunk; ++c) {
             if (k0 + c < nk) {
-                const bf8 ah = __builtin_bit_cast(bf8, opx[c][0]);
-                const bf8 al = __builtin_bit_cast(bf8, opx[c][1]);
+                const bf8 ah = __builtin_bit_cast(bf8, kSplit ? opx[kSplit ? c : 0][0]
+                                                              : xs[c][0][lane]);
+                const bf8 al = __builtin_bit_cast(bf8, kSplit ? opx[kSplit ? c : 0][1]
+                                                              : xs[c][1][lane]);
                 const bf8 bh = __builtin_bit_cast(bf8, opt[c][0]);
                 const bf8 bl = __builtin_bit_cast(bf8, opt[c][1]);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
@@ -1372,16 +1381,16 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
     const int pa = hsel < 0 ? 0 : (hsel < g.in_hcu ? hsel : g.in_hcu - 1);
     int pr[16];
     float pe[16], po[kSplit ? 1 : 16];
+    auto request_old = [&]() {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        pr[r] = half_broadcast(pa, 8 * (r >> 2) + (r & 3), lane);
-        if constexpr (kSplit) {
-            pe[r] = a.pij[(int64_t)(2 * pr[r] + par) * n_out + jb];
-        } else {
-            pe[r] = a.pij[(int64_t)(2 * pr[r]) * n_out + jb];
-            po[r] = a.pij[(int64_t)(2 * pr[r] + 1) * n_out + jb];
+        for (int r = 0; r < 16; ++r) {
+            pr[r] = half_broadcast(pa, 8 * (r >> 2) + (r & 3), lane);
+            const int64_t e = (int64_t)(2 * pr[r] + par) * n_out + jb;
+            pe[r] = a.pij[e];
+            if constexpr (!kSplit) po[r] = a.pij[e + n_out];
         }
-    }
+    };
+    if constexpr (kSplit) request_old();
     gather_x(0, pa);
     // marginal inputs.  Split: lanes 0..31 the stored unit of row jl's input HCU, 32..63 the
     // block's columns.  Otherwise: lane l the unit 2 pa + l / 32 (both units of row jl's input
@@ -1392,9 +1401,6 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
     if constexpr (kSplit) {
         marginal_request(mr, row_lane ? a.ops.x_sum : a.ops.t_sum, row_lane ? n_in : n_out,
                          row_lane ? urow : jb, nk, row_lane ? a.pi_old : a.pj_old);
-    } else {
-        marginal_request(mr, a.ops.x_sum, n_in, urow, nk, a.pi_old);
-        marginal_request(mc, a.ops.t_sum, n_out, jb, nk, a.pj_old);
     }
 
     lds_barrier();
@@ -1435,6 +1441,9 @@ trace_active_pair_kernel(Geometry g, TraceArgs a, const int32_t* __restrict__ ac
                 }
             }
         } else {
+            request_old();
+            marginal_request(mr, a.ops.x_sum, n_in, urow, nk, a.pi_old);
+            marginal_request(mc, a.ops.t_sum, n_out, jb, nk, a.pj_old);
             const float lp = fast_log(fmaxf(marginal_value(mr, a.ops.x_sum, n_in, urow, nk, a), a.eps));
             const float st = marginal_colsum(mc, a.ops.t_sum, n_out, jb, nk);
             const float lpj = fast_log(fmaxf(marginal_from_colsum(mc, st, a), a.eps));
