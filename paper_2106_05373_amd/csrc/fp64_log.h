@@ -1,5 +1,6 @@
 // Natural logarithm of a positive normal double, about one ulp from the correctly rounded value
-// (host and device, so that a host test can check it against the C library).  The method is the
+// (host and device, so that a host test can check it against the C library); the kernel takes the
+// table form further down, and this one stays as the form without a table.  The method is the
 // argument reduction and s = f / (2 + f) form of the public-domain fdlibm e_log.c (Sun
 // Microsystems, 1993), with its split of ln 2 into a 32-bit head and a tail; the polynomial here
 // is the plain atanh Taylor series, not fdlibm's minimax coefficients.
