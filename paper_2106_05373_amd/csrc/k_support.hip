@@ -320,8 +320,10 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
         const float inv = 1.0f / row16_sum(e);
         if (y && in) y[o] = e * inv;
     } else {
-        float bv = in ? sv : -INFINITY;
-        int bi = in && sv > -INFINITY ? tid : 0x7fffffff;
+        // (a NaN takes no part, wherever it stands)
+        const bool part = in && sv > -INFINITY;
+        float bv = part ? sv : -INFINITY;
+        int bi = part ? tid : 0x7fffffff;
         for (int off = kThinColumns / 2; off > 0; off >>= 1) {
             const float ov = __shfl_xor(bv, off, 64);
             const int oi = __shfl_xor(bi, off, 64);

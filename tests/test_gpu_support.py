@@ -95,3 +95,24 @@ def test_supervised_batches_without_activities_leave_the_same_state(in_mcu, pair
         pair.close()
     for k, v in states[0].items():
         assert np.array_equal(v, states[1][k]), k
+
+
+@pytest.mark.parametrize("k", [30, 5])           # row by row, and by row tiles
+def test_readout_passes_over_columns_that_are_nan(k):
+    """An infinite input unit makes the support +inf, -inf or (weight 0) NaN by the sign of its
+    weight: the winner is the first +inf column, whatever NaN columns stand before it."""
+    hin, min_, mout, B = 30, 100, 10, 5
+    rng = np.random.default_rng(k)
+    mask = np.zeros((hin, 1), np.uint8)
+    mask[:k] = 1
+    pair = Pair(gpu_config(hin, min_, 1, mout, B), mask)
+    st = given_state(rng, hin, min_, 1, mout, mask)
+    st["w"][7] = [0, -1, 0, 2, -1, 0, 2, 1, -1, 0]
+    pair.ora.set_state(st)
+    pair.sync_gpu_to_oracle()
+    x = rng.random((B, hin * min_)).astype(np.float32)
+    x[:, 7] = np.inf
+    win = pair.torch.empty((B, 1), device="cuda", dtype=pair.torch.int32)
+    pair.gpu.readout(pair.dev(x), win)
+    assert (win.cpu().numpy() == 3).all()
+    pair.close()
