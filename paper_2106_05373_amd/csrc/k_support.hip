@@ -238,6 +238,38 @@ split_kernel(Geometry g, const float* __restrict__ x, int32_t B, const float* __
     stamp_end<kStamp>(stamp);
 }
 
+constexpr int kThinThreads = 512;
+constexpr int kThinColumns = 16;
+
+// The last step of the row-by-row kernels, by 16 lanes: column tid of `row` of hidden HCU hj has the
+// sum v; its support, then the softmax or argmax.
+__device__ __forceinline__ void thin_finish(const Geometry& g, int row, int hj, int tid, double v,
+                                            float bias, float gain, int mode, float* y, float* s,
+                                            int32_t* winner) {
+    const int M = g.out_mcu;
+    const bool in = tid < M;
+    const int64_t o = (int64_t)row * g.n_out + (int64_t)hj * M + tid;
+    const float sv = (float)(v + (double)bias);
+    if (s && in) s[o] = sv;
+    if (mode == 0) {
+        const float mx = row16_max(in ? sv : -INFINITY);
+        const float e = in ? expf(gain * (sv - mx)) : 0.0f;
+        const float inv = 1.0f / row16_sum(e);
+        if (y && in) y[o] = e * inv;
+    } else {
+        // (a NaN takes no part, wherever it stands)
+        const bool part = in && sv > -INFINITY;
+        float bv = part ? sv : -INFINITY;
+        int bi = part ? tid : 0x7fffffff;
+        for (int off = kThinColumns / 2; off > 0; off >>= 1) {
+            const float ov = __shfl_xor(bv, off, 64);
+            const int oi = __shfl_xor(bi, off, 64);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+        if (tid == 0) winner[(int64_t)row * g.out_hcu + hj] = bi;
+    }
+}
+
 // A narrow hidden HCU with many active units and a small batch (a readout: 3000 units to 10
 // classes, 128 rows): by row tiles it would fill a handful of CUs, each with a long chain of
 // chunks.  Here a workgroup takes one row: a thread accumulates all M_out (<= 16) columns of its
@@ -246,8 +278,6 @@ split_kernel(Geometry g, const float* __restrict__ x, int32_t B, const float* __
 // then take the softmax or argmax.  Nothing waits between the loads and the reduction, and the
 // weights are read by every workgroup from L2.  Measured at 128 rows,
 // 3000 -> 10: 11 us (in chunks of units, 8 workgroups: 25 us; one column tile per wave: 87 us).
-constexpr int kThinThreads = 512;
-constexpr int kThinColumns = 16;
 template <int W>
 __global__ void __launch_bounds__(kThinThreads)
 support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __restrict__ w,
@@ -310,27 +340,82 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < kThinThreads / 64; ++q) v += sums[q][tid];
-    const bool in = tid < M;
-    const int64_t o = (int64_t)row * g.n_out + (int64_t)hj * M + tid;
-    const float sv = (float)(v + (double)bias[(int64_t)hj * M + (in ? tid : 0)]);
-    if (s && in) s[o] = sv;
-    if (mode == 0) {
-        const float mx = row16_max(in ? sv : -INFINITY);
-        const float e = in ? expf(gain * (sv - mx)) : 0.0f;
-        const float inv = 1.0f / row16_sum(e);
-        if (y && in) y[o] = e * inv;
-    } else {
-        // (a NaN takes no part, wherever it stands)
-        const bool part = in && sv > -INFINITY;
-        float bv = part ? sv : -INFINITY;
-        int bi = part ? tid : 0x7fffffff;
-        for (int off = kThinColumns / 2; off > 0; off >>= 1) {
-            const float ov = __shfl_xor(bv, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    thin_finish(g, row, hj, tid, v, bias[(int64_t)hj * M + (tid < M ? tid : 0)], gain, mode, y, s, winner);
+}
+
+// The same for a layer whose single hidden HCU sees every input unit (M_out of 4 to 16): its weights
+// are then one contiguous array, read 16 bytes per lane.  T threads, T the largest up to 512 whose
+// 4 T elements are whole rows, so that a thread keeps its four columns from pass to pass and needs
+// two inputs per pass (its elements span at most two units); the passes' loads go out together.  The
+// threads' sums are [4 T / M][M] in LDS, added up by 32 lanes per column.  Elements past the last
+// whole vector belong to the last unit and are added at the end.
+template <int kBatch>
+__device__ __forceinline__ void flat_passes(const float* __restrict__ xrow, const f4* __restrict__ w4,
+                                            int n_vec, int n_pass, int T, int M, int n_in, int tid,
+                                            double (&acc)[4]) {
+    const int U = 4 * T / M;                                   // units per pass
+    const int u0 = 4 * tid / M, u3 = (4 * tid + 3) / M;
+    for (int p0 = 0; p0 < n_pass; p0 += kBatch) {
+        f4 wv[kBatch];
+        float xa[kBatch], xb[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {                     // (past the end: the last vector)
+            const int v = tid + T * (p0 + q);
+            wv[q] = w4[v < n_vec ? v : n_vec - 1];
+            const int a = u0 + U * (p0 + q), b = u3 + U * (p0 + q);
+            xa[q] = xrow[a < n_in ? a : n_in - 1];
+            xb[q] = xrow[b < n_in ? b : n_in - 1];
         }
-        if (tid == 0) winner[(int64_t)row * g.out_hcu + hj] = bi;
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const bool in = tid + T * (p0 + q) < n_vec;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float xe = (4 * tid + e) / M == u0 ? xa[q] : xb[q];
+                acc[e] = fma((double)(in ? xe : 0.0f), (double)(in ? wv[q][e] : 0.0f), acc[e]);
+            }
+        }
     }
+}
+
+__global__ void __launch_bounds__(kThinThreads)
+support_flat_kernel(Geometry g, const float* __restrict__ x, const float* __restrict__ w,
+                    const float* __restrict__ bias, int T, float gain, int mode,
+                    float* __restrict__ y, float* __restrict__ s, int32_t* __restrict__ winner) {
+    __shared__ double part[4 * kThinThreads];
+    __shared__ double sums[kThinThreads / 64][kThinColumns];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = blockIdx.x;
+    const int M = g.out_mcu, n_in = (int)g.n_in;
+    const float* xrow = x + (int64_t)row * n_in;
+    const int n_vec = n_in * M / 4;
+    const int n_pass = (n_vec + T - 1) / T;
+    const int c = tid & (kThinColumns - 1), cc = c < M ? c : 0;
+    const float bias_c = bias[cc];
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (tid < T) {
+        const f4* w4 = reinterpret_cast<const f4*>(w);
+        if (n_pass > 8) flat_passes<16>(xrow, w4, n_vec, n_pass, T, M, n_in, tid, acc);
+        else flat_passes<8>(xrow, w4, n_vec, n_pass, T, M, n_in, tid, acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[4 * tid + e] = acc[e];
+    }
+    lds_barrier();
+    double v = 0.0;
+    const int U = 4 * T / M;
+    for (int r = tid / kThinColumns; r < U; r += kThinThreads / kThinColumns) v += part[r * M + cc];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (lane < kThinColumns) sums[wave][lane] = v;
+    lds_barrier();
+    if (tid >= kThinColumns) return;
+    v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kThinThreads / 64; ++q) v += sums[q][tid];
+    const int rest = n_in * M - 4 * n_vec;                     // columns M - rest .. of the last unit
+    if (tid < M && tid >= M - rest)
+        v = fma((double)xrow[n_in - 1], (double)w[(int64_t)(n_in - 1) * M + tid], v);
+    thin_finish(g, row, 0, tid, v, bias_c, gain, mode, y, s, winner);
 }
 
 // kR: row tiles per workgroup.  kV: input elements per load (2 when input HCUs have an even number
@@ -1013,6 +1098,12 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
         const int width = g.out_mcu % 4 == 0 && g.n_out % 4 == 0 ? 4
                           : g.out_mcu % 2 == 0 && g.n_out % 2 == 0 ? 2 : 1;
         const uint32_t magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
+        if (max_active == g.in_hcu && g.out_mcu >= 4) {        // (counts never exceed max_active)
+            const int whole = g.out_mcu % 4 == 0 ? g.out_mcu / 4 : g.out_mcu % 2 == 0 ? g.out_mcu / 2 : g.out_mcu;
+            return launch_timed(support_flat_kernel, dim3((unsigned)B), dim3(kThinThreads), 0, stream,
+                                start, stop, g, x, w, bias, kThinThreads / whole * whole, gain, mode, y,
+                                s, winner);
+        }
         return launch_timed(width == 4 ? support_thin_kernel<4>
                             : width == 2 ? support_thin_kernel<2> : support_thin_kernel<1>,
                             dim3((unsigned)(B * g.out_hcu)), dim3(kThinThreads), 0, stream, start, stop,

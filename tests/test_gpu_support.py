@@ -42,6 +42,9 @@ SHAPES = [
     (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
     # a readout, row by row: weight rows of 16, 8 and 4 bytes, ragged batches
     (30, 100, 1, 16, 30, 40), (30, 100, 1, 10, 30, 128), (50, 13, 1, 7, 49, 19), (600, 1, 1, 2, 513, 1),
+    # ... every input unit active: weights past the last 16 bytes, 2 to 96 passes, widths 3 (not 4) to 16
+    (105, 5, 1, 13, 105, 3), (513, 1, 1, 7, 513, 2), (6000, 2, 1, 4, 6000, 3), (256, 2, 1, 6, 256, 5),
+    (12288, 1, 1, 16, 12288, 3), (40, 100, 1, 15, 40, 2), (171, 3, 1, 3, 171, 9),
     # more active units than the larger stages leave room for in the unit table
     (6000, 2, 1, 40, 5900, 18), (12288, 1, 2, 20, 12288, 3),
 ]
@@ -97,7 +100,7 @@ def test_supervised_batches_without_activities_leave_the_same_state(in_mcu, pair
         assert np.array_equal(v, states[1][k]), k
 
 
-@pytest.mark.parametrize("k", [30, 5])           # row by row, and by row tiles
+@pytest.mark.parametrize("k", [30, 29, 5])       # row by row: all units, some; by row tiles
 def test_readout_passes_over_columns_that_are_nan(k):
     """An infinite input unit makes the support +inf, -inf or (weight 0) NaN by the sign of its
     weight: the winner is the first +inf column, whatever NaN columns stand before it."""
