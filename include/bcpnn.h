@@ -193,6 +193,15 @@ bcpnn_status bcpnn_structural_update_static(bcpnn_layer *layer, int32_t *n_swapp
 bcpnn_status bcpnn_readout(bcpnn_layer *layer, const float *x_dev, int32_t B,
                            int32_t *winner_dev);
 
+/* Inference of a two-layer network: winner_dev [B] receives the readout's argmax over the hidden
+ * activities of x_dev [B][n_in] (any B >= 1), as forward on hidden and readout on readout give it.
+ * The readout has one hidden HCU and hidden's units as its inputs; both layers are on one stream.
+ * y_dev [rows][hidden n_out] holds the activities of up to `rows` samples at a time, which may be
+ * more than max_batch; x_dev and y_dev are 16-byte aligned.  Allocates nothing, enqueues only (and
+ * can be captured, as forward can).  Errors: EINVAL, ESTATE, EDEVICE. */
+bcpnn_status bcpnn_predict(bcpnn_layer *hidden, bcpnn_layer *readout, const float *x_dev,
+                           int32_t B, float *y_dev, int32_t rows, int32_t *winner_dev);
+
 /* Applies the queued silent-block updates of Pij (train_batch defers them; see "Second stream"
  * above) and makes the caller's stream wait for them: work enqueued on that stream after this
  * call sees every Pij as per-batch updates leave it.  It enqueues only and does not wait for

@@ -28,7 +28,7 @@ STATUS = {0: "BCPNN_OK", -1: "BCPNN_EINVAL", -2: "BCPNN_ENOMEM", -3: "BCPNN_EDEV
 EXPORTS = [
     "bcpnn_config_default", "bcpnn_layer_create", "bcpnn_layer_destroy", "bcpnn_forward",
     "bcpnn_train_batch", "bcpnn_recompute_weights", "bcpnn_structural_update",
-    "bcpnn_structural_update_static", "bcpnn_readout", "bcpnn_flush", "bcpnn_get_state",
+    "bcpnn_structural_update_static", "bcpnn_readout", "bcpnn_predict", "bcpnn_flush", "bcpnn_get_state",
     "bcpnn_set_state", "bcpnn_get_mi", "bcpnn_profile_enable", "bcpnn_profile_read",
     "bcpnn_profile_read_kernel", "bcpnn_last_error",
 ]
@@ -74,6 +74,7 @@ def _load() -> ctypes.CDLL:
         "bcpnn_recompute_weights": (i32, [vp]),
         "bcpnn_structural_update": (i32, [vp, ctypes.POINTER(i32)]),
         "bcpnn_readout": (i32, [vp, vp, i32, vp]),
+        "bcpnn_predict": (i32, [vp, vp, vp, i32, vp, i32, vp]),
         "bcpnn_flush": (i32, [vp]),
         "bcpnn_structural_update_static": (i32, [vp, vp]),
         "bcpnn_get_state": (i32, [vp, ctypes.POINTER(StateView)]),
@@ -214,6 +215,14 @@ class Layer:
         B = x.shape[0]
         _check(lib.bcpnn_readout(self._h, _dev_ptr(x, "x", torch.float32, (B, self.n_in)), B,
                                  _dev_ptr(winner, "winner", torch.int32, (B, self.cfg.out_hcu))))
+
+    def predict_with(self, readout, x, y, winner):
+        """winner [B]: the argmax of the layer `readout` over this layer's activities of x [B][n_in],
+        as many rows per launch as the workspace y [rows][n_out] has."""
+        B = x.shape[0]
+        _check(lib.bcpnn_predict(self._h, readout._h, _dev_ptr(x, "x", torch.float32, (B, self.n_in)), B,
+                                 _dev_ptr(y, "y", torch.float32, (y.shape[0], self.n_out)), y.shape[0],
+                                 _dev_ptr(winner, "winner", torch.int32, (B,))))
 
     def flush(self):
         """Applies the queued silent-block updates of Pij on the layer's stream (no host wait)."""

@@ -723,6 +723,46 @@ bcpnn_status bcpnn_readout(bcpnn_layer* L, const float* x_dev, int32_t B, int32_
     return BCPNN_OK;
 }
 
+// More rows per launch than max_batch, which bounds the training buffers and no forward pass: a
+// launch of 128 rows is bound by its round trips, one of 1024 by the matrix rate.
+bcpnn_status bcpnn_predict(bcpnn_layer* hidden, bcpnn_layer* readout, const float* x_dev, int32_t B,
+                           float* y_dev, int32_t rows, int32_t* winner_dev) {
+    if (bcpnn_status st = usable(hidden)) return st;
+    if (bcpnn_status st = usable(readout)) return st;
+    if (!x_dev || !y_dev || !winner_dev)
+        return fail(BCPNN_EINVAL, "x_dev, y_dev and winner_dev are required");
+    if (misaligned(x_dev) || misaligned(y_dev))
+        return fail(BCPNN_EINVAL, "device buffers must be 16-byte aligned");
+    const Geometry &gh = hidden->g, &gr = readout->g;
+    if (gr.n_in != gh.n_out || gr.out_hcu != 1 || readout->stream != hidden->stream)
+        return fail(BCPNN_EINVAL, "the readout must have one HCU over the hidden units, on one stream");
+    if (B < 1 || rows < 1) return fail(BCPNN_EINVAL, "B and rows must be positive");
+    // Rows per launch, even over the launches: whole row tiles, or as few as keep x 16-byte aligned,
+    // within the limits of a launch: 32-bit byte offsets into its inputs and 2^23 workgroups.
+    const int64_t widest = std::max(gh.n_in, gr.n_in);
+    const int64_t most = std::min((int64_t)(UINT32_MAX / 4) / widest, ((int64_t)1 << 27) / gh.out_hcu);
+    int64_t step = std::min<int64_t>({rows, B, most / 16 * 16});
+    if (step < B) {
+        const int64_t unit = step >= 16 ? 16 : gh.n_in % 4 == 0 ? 1 : gh.n_in % 2 == 0 ? 2 : 4;
+        step = step / unit * unit;
+        if (step == 0) return fail(BCPNN_EINVAL, "y_dev has too few rows for aligned inputs");
+        const int64_t launches = (B + step - 1) / step;
+        step = ((B + launches - 1) / launches + unit - 1) / unit * unit;
+    }
+    for (int64_t k = 0; k < B; k += step) {
+        const int32_t n = (int32_t)std::min<int64_t>(step, B - k);
+        HIP_TRY(hidden, bcpnn::launch_support(hidden->stream, gh, x_dev + k * gh.n_in, n, hidden->w,
+                                              hidden->b, hidden->act_list, hidden->act_count,
+                                              hidden->max_active, hidden->cfg.gain, 0, y_dev, nullptr,
+                                              nullptr, nullptr, nullptr));
+        HIP_TRY(readout, bcpnn::launch_support(readout->stream, gr, y_dev, n, readout->w, readout->b,
+                                               readout->act_list, readout->act_count,
+                                               readout->max_active, readout->cfg.gain, 1, nullptr,
+                                               nullptr, winner_dev + k, nullptr, nullptr));
+    }
+    return BCPNN_OK;
+}
+
 bcpnn_status bcpnn_flush(bcpnn_layer* L) {
     if (bcpnn_status st = usable(L)) return st;
     HIP_TRY(L, join_side(L));

@@ -104,6 +104,7 @@ def test_null_layer_calls_are_rejected(b):
     assert L.bcpnn_recompute_weights(None) == -1
     assert L.bcpnn_structural_update(None, None) == -1
     assert L.bcpnn_readout(None, None, 1, None) == -1
+    assert L.bcpnn_predict(None, None, None, 1, None, 1, None) == -1
     assert L.bcpnn_get_mi(None, None) == -1
     assert L.bcpnn_flush(None) == -1
     assert L.bcpnn_layer_create(None, None, None, None) == -1
