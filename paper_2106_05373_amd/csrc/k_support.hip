@@ -85,7 +85,8 @@ struct SupportLayout {
     int parts;                     // waves that share a tile's k-steps; groups * parts waves
     int kc;                        // units per chunk
     int n_chunks;
-    int k_alloc;                   // unit table: the chunks, the last in whole runs of 64 units
+    int win;                       // chunks whose units the table holds at a time
+    int k_alloc;                   // unit table: those chunks, the last in whole runs of 64 units
     int max_k;                     // largest number of active units of a hidden HCU
     uint32_t mcu_magic;            // ceil(2^32 / in_mcu) (0 for in_mcu = 1)
     int per;                       // k-steps of a share in a whole chunk
@@ -476,14 +477,19 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
     const int32_t* alist = act_list + (int64_t)hj * g.in_hcu;
     const int64_t col_base = (int64_t)hj * g.out_mcu;
     // The table is filled up to the largest K_h of the layer (and past it, with its first entry),
-    // so its loads do not wait for the count; entries past k_total take no part.
+    // so its loads do not wait for the count; entries past k_total take no part.  It begins at
+    // unit k_tab: where it has no room for all of them, it is filled again every lay.win chunks.
     int32_t* units = kMulti ? reinterpret_cast<int32_t*>(dyn) : utab;
     const int k_alloc = kMulti ? lay.k_alloc : (kc + 63) & ~63;
-    for (int32_t k = tid; k < k_alloc; k += n_thr) {
-        const int32_t kk = k < lay.max_k ? k : 0;
-        const int32_t h = lay.mcu_magic ? (int32_t)__umulhi((uint32_t)kk, lay.mcu_magic) : kk;
-        units[k] = (alist[h] - h) * g.in_mcu + kk;
-    }
+    int k_tab = 0;
+    auto fill_units = [&]() __attribute__((always_inline)) {
+        for (int32_t k = tid; k < k_alloc; k += n_thr) {
+            const int32_t kk = k_tab + k < lay.max_k ? k_tab + k : 0;
+            const int32_t h = lay.mcu_magic ? (int32_t)__umulhi((uint32_t)kk, lay.mcu_magic) : kk;
+            units[k] = (alist[h] - h) * g.in_mcu + kk;
+        }
+    };
+    fill_units();
     // Column of tile t of this wave (a tile past the last repeats it, its result discarded).
     int col_of[kTPW];
     float bias_r[kTPW];
@@ -517,13 +523,13 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
             char* dst = reinterpret_cast<char*>(st) + 4 * kS * kRowsPer * wave;
             int r = kRowsPer * wave + lr;
             const int dr = kRowsPer * n_waves;
-            uint32_t u_next = (uint32_t)units[k0 + (r < live ? r : 0)];
+            uint32_t u_next = (uint32_t)units[k0 - k_tab + (r < live ? r : 0)];
             for (int first = kRowsPer * wave; first < live; first += dr) {
                 const uint32_t u = u_next;
                 const int c = kRotate ? (c0 - 16 * (r & 3)) & (kS - 1) : c0;
                 const bool in = r < live && c < g.out_mcu;
                 r += dr;
-                u_next = (uint32_t)units[k0 + (r < live ? r : 0)];
+                u_next = (uint32_t)units[k0 - k_tab + (r < live ? r : 0)];
                 const char* src = reinterpret_cast<const char*>(
                     wb + (uint64_t)u * row_bytes + 4u * (uint32_t)c);
                 if (in) {
@@ -540,7 +546,7 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
             constexpr int kPieces = (kRowVecs + 63) / 64;
             for (int first = wave; first < live; first += 64 * n_waves) {
                 const int mine = first + n_waves * lane;
-                const int ul = units[k0 + (mine < live ? mine : 0)];
+                const int ul = units[k0 - k_tab + (mine < live ? mine : 0)];
                 int i = 0;
                 for (int r = first; r < live && i < 64; r += n_waves, ++i) {
                     uint64_t row = wb + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ul, i) * row_bytes;
@@ -611,7 +617,7 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
     auto request_x = [&](int k0, f4* st) __attribute__((always_inline)) {
         float* xp = reinterpret_cast<float*>(st) + kc * kS;
         for (int kb = 0; kb < kc; kb += 64) {
-            const uint32_t off = (uint32_t)units[k0 + kb + lane] * 4u;
+            const uint32_t off = (uint32_t)units[k0 - k_tab + kb + lane] * 4u;
             const bool in = kb + lane < kc;
             for (int row = wave; row < x_live; row += n_waves) {
                 const char* src = reinterpret_cast<const char*>(x + (int64_t)(row0 + row) * g.n_in) + off;
@@ -724,6 +730,11 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
             __builtin_amdgcn_s_waitcnt(0);
             lds_barrier();
             if ((c + 1) * kc < k_total) {
+                if ((c + 1) * kc - k_tab >= lay.win * kc) {    // (every wave is done with the table)
+                    k_tab = (c + 1) * kc;
+                    fill_units();
+                    lds_barrier();
+                }
                 request_w((c + 1) * kc, next);
                 request_x((c + 1) * kc, next);
             }
@@ -1002,7 +1013,9 @@ bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayo
     }
     L.xstride = stride(L.kc);
     L.n_chunks = (L.max_k + L.kc - 1) / L.kc;
-    L.k_alloc = (L.kc * (L.n_chunks - 1) + (L.kc + 63) / 64 * 64 + 63) / 64 * 64;
+    auto entries = [&](int chunks) { return (L.kc * (chunks - 1) + (L.kc + 63) / 64 * 64 + 63) / 64 * 64; };
+    L.win = L.n_chunks;
+    L.k_alloc = entries(L.n_chunks);
     const int steps = (L.kc + 3) / 4;                          // no share without a k-step
     if (L.parts > steps) L.parts = steps;
     L.per = (steps + L.parts - 1) / L.parts;
@@ -1015,6 +1028,16 @@ bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayo
     L.row_major = !shape_one(v);
     if (n_main > INT32_MAX / 2) return false;
     L.n_main = (int)n_main;
+    // A table of every unit may leave no room for the stages (with one row tile, above 3500 units):
+    // it then holds as many chunks' as fit (546x10 inputs, 4490 units active, 1x27, 144 rows: 105
+    // us; four row tiles per workgroup, whose stages leave room, 269).
+    if (!shape_one(v)) {
+        const int64_t room = ((int64_t)kLdsLimit - 16 - 2 * stage_bytes(kR, ps)) / 4;
+        if (kR == 1 && L.k_alloc > room) {
+            L.win = room - 128 >= L.kc ? (int)((room - 128) / L.kc) : 1;
+            L.k_alloc = entries(L.win);
+        }
+    }
     const size_t table = shape_one(v) ? 0 : (size_t)L.k_alloc * 4;
     const size_t panel = shape_one(v) ? (size_t)bytes(L.kc) : 0;
     const size_t vals = v == kFewOne || v == kFewChunks ? (size_t)tpw : (size_t)4 * kR * tpw;
@@ -1132,7 +1155,7 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
     if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
     take(kOneChunk);
     take(kChunks);
-    take(kManyRows);      // (a unit table that leaves no room for the larger stages)
+    take(kManyRows);      // (where the stages of one row tile leave no room for its sums)
     if (shape < 0) return hipErrorInvalidValue;
     const int stride = panel_stride(g.out_mcu), xv = input_vec(g);
     const int n_waves = lay.groups * lay.parts;

@@ -46,7 +46,9 @@ SHAPES = [
     (105, 5, 1, 13, 105, 3), (513, 1, 1, 7, 513, 2), (6000, 2, 1, 4, 6000, 3), (256, 2, 1, 6, 256, 5),
     (12288, 1, 1, 16, 12288, 3), (40, 100, 1, 15, 40, 2), (171, 3, 1, 3, 171, 9),
     # more active units than the larger stages leave room for in the unit table
-    (6000, 2, 1, 40, 5900, 18), (12288, 1, 2, 20, 12288, 3),
+    # (the table then holds a part of them at a time)
+    (6000, 2, 1, 40, 5900, 18), (12288, 1, 2, 20, 12288, 3), (5000, 1, 2, 11, 4801, 1),
+    (1200, 3, 2, 93, 1195, 15), (360, 10, 1, 27, 359, 40), (3500, 1, 2, 100, 3454, 17),
 ]
 
 
@@ -73,6 +75,21 @@ def test_forward_and_readout_match_oracle(shape):
     pair.gpu.readout(pair.dev(x), win)
     best = s.reshape(B, hout, mout).argmax(2)    # the argmax of the GPU's own support: exact
     assert np.array_equal(win.cpu().numpy(), best)
+    pair.close()
+
+
+def test_training_batch_of_more_units_than_the_table_holds():
+    rng = np.random.default_rng(8)
+    hin, hout, mout, k, B = 4100, 2, 21, 4011, 19
+    mask = np.stack([synth.random_mask(hin, 1, k, 60 + c)[:, 0] for c in range(hout)], 1)
+    pair = Pair(gpu_config(hin, 1, hout, mout, B, alpha=0.05), mask)
+    pair.ora.set_state(given_state(rng, hin, 1, hout, mout, mask))
+    pair.sync_gpu_to_oracle()
+    y, y_o, _ = pair.train(rng.random((B, hin)).astype(np.float32))
+    assert max_abs(y, y_o) <= TOL_ACT
+    got, want = pair.gpu.get_state(), pair.ora.get_state()
+    for key in ("pi", "pj", "pij"):
+        assert max_abs(got[key], want[key]) <= TOL_ACT, key
     pair.close()
 
 
