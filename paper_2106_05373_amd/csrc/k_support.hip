@@ -1155,7 +1155,6 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
     if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
     take(kOneChunk);
     take(kChunks);
-    take(kManyRows);      // (where the stages of one row tile leave no room for its sums)
     if (shape < 0) return hipErrorInvalidValue;
     const int stride = panel_stride(g.out_mcu), xv = input_vec(g);
     const int n_waves = lay.groups * lay.parts;
