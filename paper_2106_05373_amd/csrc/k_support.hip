@@ -85,8 +85,7 @@ struct SupportLayout {
     int parts;                     // waves that share a tile's k-steps; groups * parts waves
     int kc;                        // units per chunk
     int n_chunks;
-    int win;                       // chunks whose units the table holds at a time
-    int k_alloc;                   // unit table: those chunks, the last in whole runs of 64 units
+    int k_alloc;                   // unit table: win chunks, the last in whole runs of 64 units
     int max_k;                     // largest number of active units of a hidden HCU
     uint32_t mcu_magic;            // ceil(2^32 / in_mcu) (0 for in_mcu = 1)
     int per;                       // k-steps of a share in a whole chunk
@@ -99,6 +98,7 @@ struct SupportLayout {
     int row_major;                 // workgroup order: hidden HCUs of a row group together
     int n_main;                    // support workgroups; those past it split the input
     int n_row_tiles;
+    int win;                       // chunks whose units the table holds at a time
 };
 
 typedef void __attribute__((address_space(3))) lds_void;
