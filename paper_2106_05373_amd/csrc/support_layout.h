@@ -1,0 +1,183 @@
+// How a support launch covers its rows and units: the kernel's forms, the sizes of their LDS buffers
+// and the choice among them (host code, but for the constants; k_support.hip has the kernels).
+#pragma once
+
+#include <initializer_list>
+
+#include "bcpnn_internal.h"
+
+namespace bcpnn {
+
+constexpr int kRows = 16;          // batch rows per row tile
+constexpr int kMaxWaves = 16;
+// (row tile, hidden HCU) items from which kR = 4 pays: its workgroups, a quarter of the items, have
+// to fill the CUs (8192 rows x 30 HCUs, 15360 items: 270 us against 430 with kR = 2)
+constexpr int64_t kManyRowTiles = 1024;
+constexpr int kCus = 256;                 // compute units
+constexpr int kMinSplit = 16;             // least workgroups for the input's split
+constexpr int kOneUnits = 1024;           // unit table of the one-chunk variants
+constexpr int kOneBytes = 120 * 1024;     // their panels and table
+constexpr int kManyTiles = 4;             // row tiles per workgroup of the many-rows variant
+// Bytes of a stage buffer: with one row tile the launch has few workgroups and takes most of a CU's
+// LDS (the chunks are then few); with kManyTiles two workgroups share a CU; wide hidden HCUs leave
+// room for the longest unit table.
+constexpr int stage_bytes(int rows, int stride) {
+    return rows > 1 ? 26 * 1024 : stride > 128 ? 36 * 1024 : 73 * 1024;
+}
+constexpr int kXRegs = 12;                // input elements a thread holds per chunk
+
+struct SupportLayout {
+    int n_tiles;                   // 16-column tiles of a hidden HCU
+    int groups;                    // waves that share the column tiles (tile t: wave t mod groups)
+    int parts;                     // waves that share a tile's k-steps; groups * parts waves
+    int kc;                        // units per chunk
+    int n_chunks;
+    int k_alloc;                   // unit table: win chunks, the last in whole runs of 64 units
+    int max_k;                     // largest number of active units of a hidden HCU
+    uint32_t mcu_magic;            // ceil(2^32 / in_mcu) (0 for in_mcu = 1)
+    int per;                       // k-steps of a share in a whole chunk
+    int vec4;                      // weight rows move 16 bytes per lane
+    int rw, x_slots;               // input rows per wave, loads per thread and chunk
+    int xstride, mpad;             // LDS row strides of the input panel and the support tile
+    int n_split;                   // workgroups that split the input
+    int sum_order;                 // of the input's column sums
+    int n_row_groups;              // groups of kR row tiles
+    int row_major;                 // workgroup order: hidden HCUs of a row group together
+    int n_main;                    // support workgroups; those past it split the input
+    int n_row_tiles;
+    int win;                       // chunks whose units the table holds at a time
+};
+
+constexpr size_t kLdsLimit = 160 * 1024;   // LDS of one gfx950 workgroup
+
+// How a launch covers its rows and units.
+enum Shape { kOneChunk, kChunks, kManyRows, kFewOne, kFewChunks };
+
+constexpr int shape_rows(int v) { return v == kManyRows ? kManyTiles : 1; }
+constexpr bool shape_one(int v) { return v == kOneChunk || v == kFewOne; }
+
+// The weight panel's row stride for M_out columns: 16, 80 (both 16 mod 64, so that the four rows of
+// an operand read fall on different banks), then powers of two.  (A stride per 16 columns would
+// multiply the kernels; between 16 and 80 the launch bounds such HCUs more than their panel.)
+inline int panel_stride(int out_mcu) {
+    if (out_mcu <= 80) return out_mcu <= 16 ? 16 : 80;
+    int s = 128;
+    while (s < out_mcu) s *= 2;
+    return s;
+}
+
+inline uint32_t magic_of(int d) { return (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d); }
+
+inline int input_vec(const Geometry& g) { return g.in_mcu % 2 == 0 ? 2 : 1; }
+
+// Layout of a launch in one shape and its dynamic LDS, or false when the shape does not cover the
+// sizes.
+inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayout* out,
+                        size_t* dyn_bytes) {
+    SupportLayout L{};
+    const int kR = shape_rows(v), ps = panel_stride(g.out_mcu);
+    const int tpw = ps <= 256 ? 1 : ps / 256;
+    if (v != kChunks && ps > 128) return false;
+    L.n_tiles = (g.out_mcu + 15) / 16;
+    L.groups = (L.n_tiles + tpw - 1) / tpw;
+    L.max_k = max_k > 0 ? max_k : 1;
+    L.mcu_magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
+    L.vec4 = g.out_mcu % 4 == 0 && g.n_out % 4 == 0;
+    L.mpad = (g.out_mcu + 15) / 16 * 16 + 4;
+    const int xv = input_vec(g);
+    // (2^22 workgroups of sixteen waves would be 2^32 work-items)
+    const int64_t n_main = ((int64_t)(B + kR * kRows - 1) / (kR * kRows)) * g.out_hcu;
+    const int waves = kR == 1 && !shape_one(v) && n_main < (1 << 22) - 2 * kCus ? kMaxWaves : 8;
+    L.parts = waves / L.groups > 0 ? waves / L.groups : 1;
+    // the chunk; the rows of the input panel lie 4 mod 8 words apart, so that the 16 rows x 4 units
+    // of an operand read fall on different banks
+    auto stride = [v](int kc) {
+        if (shape_one(v)) return (kc + 1) / 2 % 2 ? (kc + 1) / 2 * 2 : (kc + 1) / 2 * 2 + 2;   // fp64
+        return (kc + 3) / 4 % 2 ? (kc + 3) / 4 * 4 : (kc + 3) / 4 * 4 + 4;                     // fp32
+    };
+    const int x_bytes = shape_one(v) ? 8 : 4;              // per element of the input panel
+    auto bytes = [&](int kc) { return 4 * kc * ps + x_bytes * kR * kRows * stride(kc); };
+    L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
+    auto slots = [&](int kc) { return L.rw * ((kc + 64 * xv - 1) / (64 * xv)); };
+    const int most_slots = kXRegs / xv;
+    if (shape_one(v)) {
+        L.kc = (L.max_k + 3) / 4 * 4;
+        if (L.kc > kOneUnits || slots(L.kc) > most_slots || bytes(L.kc) + 4 * kOneUnits > kOneBytes) return false;
+    } else {
+        const int cap = stage_bytes(kR, ps);
+        L.kc = cap / (4 * ps + x_bytes * kR * kRows) / 4 * 4;
+        while (L.kc > 4 && bytes(L.kc) > cap) L.kc -= 4;
+        if (L.kc < 4 || bytes(L.kc) > cap) return false;
+        if (L.kc > (L.max_k + 3) / 4 * 4) L.kc = (L.max_k + 3) / 4 * 4;
+    }
+    L.xstride = stride(L.kc);
+    L.n_chunks = (L.max_k + L.kc - 1) / L.kc;
+    auto entries = [&](int chunks) { return (L.kc * (chunks - 1) + (L.kc + 63) / 64 * 64 + 63) / 64 * 64; };
+    L.win = L.n_chunks;
+    L.k_alloc = entries(L.n_chunks);
+    const int steps = (L.kc + 3) / 4;                          // no share without a k-step
+    if (L.parts > steps) L.parts = steps;
+    L.per = (steps + L.parts - 1) / L.parts;
+    L.parts = (steps + L.per - 1) / L.per;
+    L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
+    L.x_slots = slots(L.kc);
+    if (shape_one(v) && L.x_slots > most_slots) return false;
+    L.n_row_tiles = (B + kRows - 1) / kRows;
+    L.n_row_groups = (L.n_row_tiles + kR - 1) / kR;
+    L.row_major = !shape_one(v);
+    if (n_main > INT32_MAX / 2) return false;
+    L.n_main = (int)n_main;
+    // A table of every unit may leave no room for the stages (with one row tile, above 3500 units):
+    // it then holds as many chunks' as fit (546x10 inputs, 4490 units active, 1x27, 144 rows: 105
+    // us; four row tiles per workgroup, whose stages leave room, 269).
+    if (!shape_one(v)) {
+        const int64_t room = ((int64_t)kLdsLimit - 16 - 2 * stage_bytes(kR, ps)) / 4;
+        if (kR == 1 && L.k_alloc > room) {
+            L.win = room - 128 >= L.kc ? (int)((room - 128) / L.kc) : 1;
+            L.k_alloc = entries(L.win);
+        }
+    }
+    const size_t table = shape_one(v) ? 0 : (size_t)L.k_alloc * 4;
+    const size_t panel = shape_one(v) ? (size_t)bytes(L.kc) : 0;
+    const size_t vals = v == kFewOne || v == kFewChunks ? (size_t)tpw : (size_t)4 * kR * tpw;
+    const size_t tile = (size_t)kR * kRows * L.mpad * sizeof(float);
+    const size_t sums = (size_t)(L.parts - 1) * L.groups * vals * 64 * sizeof(double);
+    const size_t stage = shape_one(v) ? 16 : (size_t)stage_bytes(kR, ps);
+    if (!shape_one(v) && tile / 2 + (kR == 1 ? sums : 0) > stage) return false;
+    const size_t after = shape_one(v) ? tile + sums : kR > 1 ? sums : 0;
+    *dyn_bytes = table + panel > after ? table + panel : after;
+    *out = L;
+    const size_t fixed = 2 * stage + (shape_one(v) ? 4 * kOneUnits : 16);
+    return fixed + *dyn_bytes <= kLdsLimit;
+}
+
+// The form and layout of a launch and its dynamic LDS; -1 when no form covers the sizes.  ops:
+// training.
+inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, SupportLayout* lay,
+                         size_t* lds) {
+    const int64_t row_tiles = ((int64_t)B + kRows - 1) / kRows;
+    int shape = -1;
+    auto take = [&](int v) {
+        if (shape < 0 && make_layout(g, B, max_k, v, lay, lds)) shape = v;
+    };
+    if (!ops && B == 1) {
+        take(kFewOne);
+        take(kFewChunks);
+    }
+    if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
+    take(kOneChunk);
+    take(kChunks);
+    return shape;
+}
+
+// Workgroups of a training launch that split the input, beside the support's n_main: a wave per
+// task, or on the CUs that the support leaves idle.
+inline int64_t split_workgroups(const Geometry& g, const SupportLayout& lay) {
+    const int n_waves = lay.groups * lay.parts;
+    int64_t n_split = ((int64_t)lay.n_row_tiles * ((g.n_in + 63) / 64) + n_waves - 1) / n_waves;
+    if (lay.n_main < kCus && n_split > kCus - lay.n_main)
+        n_split = kCus - lay.n_main > kMinSplit ? kCus - lay.n_main : n_split < kMinSplit ? n_split : kMinSplit;
+    return n_split;
+}
+
+}  // namespace bcpnn
