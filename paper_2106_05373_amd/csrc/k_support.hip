@@ -28,7 +28,9 @@
 //  * A layer whose active units do not fit one panel streams them in chunks through two stage
 //    buffers, the next chunk's loads in flight during the products.  The buffers are separate
 //    arrays named at compile time, so that the compiler does not make a chunk's LDS reads wait
-//    for the next chunk's loads.
+//    for the next chunk's loads.  With one row tile they take most of a CU's LDS; where more
+//    workgroups than CUs follow one another, two of them share a CU with half of the stages each,
+//    for the widths that gain from it (two_per_cu).
 //  * A batch of many rows takes kR = 4: the weights are then loaded and converted once for four
 //    row tiles, and several workgroups share a CU, so that one's gather, softmax and stores pass
 //    under the others' products.
@@ -391,8 +393,9 @@ support_flat_kernel(Geometry g, const float* __restrict__ x, const float* __rest
 // of MCUs).  kS: row stride of the weight panel in LDS (panel_stride).
 // kMulti: several chunks (else the one chunk holds every active unit).  kFew: a single row, on
 // fp64 FMAs.  kOps: training (the contraction operands are written).  kStamp: the launch stamps
-// its start and end (training launches that profiling times).
-template <int kR, int kS, int kV, bool kMulti, bool kFew, bool kOps, bool kStamp>
+// its start and end (training launches that profiling times).  kPair: stages of half the size, so that
+// two workgroups share a CU.
+template <int kR, int kS, int kV, bool kMulti, bool kFew, bool kOps, bool kStamp, bool kPair = false>
 __global__ void __launch_bounds__(64 * kMaxWaves)
 support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32_t B,
                const float* __restrict__ w, const float* __restrict__ bias,
@@ -400,9 +403,9 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
                float gain, int mode, float* __restrict__ y, float* __restrict__ s,
                int32_t* __restrict__ winner, const float* __restrict__ target,
                TraceOperands ops, unsigned long long* stamp) {
-    constexpr int kTPW = kS <= 256 ? 1 : kS / 256;       // column tiles per wave
+    constexpr int kTPW = tiles_per_wave(kS);
     constexpr bool kNarrow = kS <= 128;
-    constexpr int kStage = !kMulti ? 16 : stage_bytes(kR, kS);
+    constexpr int kStage = !kMulti ? 16 : stage_bytes(kR, kPair);
     __shared__ f4 stage0[kStage / 16];
     __shared__ f4 stage1[kStage / 16];
     __shared__ int32_t utab[kMulti ? 4 : kOneUnits];
@@ -652,8 +655,17 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
         const xelem* ap = reinterpret_cast<const xelem*>(ws + kc * kS) +
                           (kFew ? 0 : lj * xstride) + 4 * first + lg;
         const float* bp = ws + (4 * first + lg) * kS;
-        // the last kSteps steps: those past the end (and units past it) take zeros
+        // the last kSteps steps.  A share of whole k-steps ends before those past its end; in a
+        // partial one these, and the units past it, take zeros.  (Blanking every share's last steps
+        // took 4 to 11%: 200 MCUs, 1000 units, 100 HCUs at 208 rows 398 against 356 us.)
         auto finish = [&](Operands& o, int ks) __attribute__((always_inline)) {
+            if (last == 4 * end) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u)
+                    if (ks + u < end) step(o.a[u], o.b[u]);
+                return;
+            }
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) {
                 const bool in = 4 * (ks + u) + lg < last;
@@ -869,7 +881,7 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
         else if (g.out_mcu <= 64) activate(Count<4>{});
         else activate(Count<8>{});
     } else {
-        activate(Count<4 * kTPW>{});
+        activate(Count<kS / 64>{});
     }
     if constexpr (kOps) {
         // Contraction operands of this workgroup's hidden HCU: its columns of t (the activity
@@ -919,6 +931,9 @@ hipError_t with_kernel(int shape, int stride, int xv, F&& f) {
             case kOneChunk: return f(support_kernel<1, S, V, false, false, kOps, kStamp>);
             case kChunks: return f(support_kernel<1, S, V, true, false, kOps, kStamp>);
             case kManyRows: return f(support_kernel<kManyTiles, S, V, true, false, kOps, kStamp>);
+            case kTwoPerCu:
+                if constexpr (S == 128) return f(support_kernel<1, S, V, true, false, kOps, kStamp, true>);
+                break;
             default: break;
         }
         if constexpr (!kOps) {
@@ -933,7 +948,9 @@ hipError_t with_kernel(int shape, int stride, int xv, F&& f) {
             case 16: return narrow(Count<16>{}, v_c);
             case 80: return narrow(Count<80>{}, v_c);
             case 128: return narrow(Count<128>{}, v_c);
-            case 256: return f(support_kernel<1, 256, V, true, false, kOps, kStamp>);
+            case 256:
+                return shape == kTwoPerCu ? f(support_kernel<1, 256, V, true, false, kOps, kStamp, true>)
+                                          : f(support_kernel<1, 256, V, true, false, kOps, kStamp>);
             case 512: return f(support_kernel<1, 512, V, true, false, kOps, kStamp>);
             case 1024: return f(support_kernel<1, 1024, V, true, false, kOps, kStamp>);
             default: return hipErrorInvalidValue;
@@ -954,7 +971,7 @@ template <bool kOps, bool kStamp>
 void raise_lds_limit() {
     for (int xv = 1; xv <= 2; ++xv)
         for (int stride : {16, 80, 128, 256, 512, 1024})
-            for (int v = kOneChunk; v <= kFewChunks; ++v)
+            for (int v = kOneChunk; v < kShapes; ++v)
                 (void)with_kernel<kOps, kStamp>(v, stride, xv, [](auto kernel) {
                     return hipFuncSetAttribute((const void*)kernel,
                                                hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -18,12 +18,14 @@ constexpr int kMinSplit = 16;             // least workgroups for the input's sp
 constexpr int kOneUnits = 1024;           // unit table of the one-chunk variants
 constexpr int kOneBytes = 120 * 1024;     // their panels and table
 constexpr int kManyTiles = 4;             // row tiles per workgroup of the many-rows variant
-// Bytes of a stage buffer: with one row tile the launch has few workgroups and takes most of a CU's
-// LDS (the chunks are then few); with kManyTiles two workgroups share a CU; wide hidden HCUs leave
-// room for the longest unit table.
-constexpr int stage_bytes(int rows, int stride) {
-    return rows > 1 ? 26 * 1024 : stride > 128 ? 36 * 1024 : 73 * 1024;
+// Bytes of a stage buffer: with one row tile a launch of few workgroups takes most of a CU's LDS (the
+// chunks are then few); kManyTiles row tiles, and the form of two workgroups per CU (`pair`), leave
+// room for a second workgroup.
+constexpr int stage_bytes(int rows, bool pair) {
+    return rows > 1 ? 26 * 1024 : pair ? 37 * 1024 : 73 * 1024;
 }
+// Column tiles per wave: a stride takes at most sixteen waves.
+constexpr int tiles_per_wave(int stride) { return stride <= 256 ? 1 : stride / 256; }
 constexpr int kXRegs = 12;                // input elements a thread holds per chunk
 
 struct SupportLayout {
@@ -51,7 +53,7 @@ struct SupportLayout {
 constexpr size_t kLdsLimit = 160 * 1024;   // LDS of one gfx950 workgroup
 
 // How a launch covers its rows and units.
-enum Shape { kOneChunk, kChunks, kManyRows, kFewOne, kFewChunks };
+enum Shape { kOneChunk, kChunks, kManyRows, kFewOne, kFewChunks, kTwoPerCu, kShapes };
 
 constexpr int shape_rows(int v) { return v == kManyRows ? kManyTiles : 1; }
 constexpr bool shape_one(int v) { return v == kOneChunk || v == kFewOne; }
@@ -76,8 +78,10 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
                         size_t* dyn_bytes) {
     SupportLayout L{};
     const int kR = shape_rows(v), ps = panel_stride(g.out_mcu);
-    const int tpw = ps <= 256 ? 1 : ps / 256;
-    if (v != kChunks && ps > 128) return false;
+    const int tpw = tiles_per_wave(ps);
+    const bool pair = v == kTwoPerCu;
+    if (v != kChunks && ps > (pair ? 256 : 128)) return false;
+    if (pair && ps < 128) return false;
     L.n_tiles = (g.out_mcu + 15) / 16;
     L.groups = (L.n_tiles + tpw - 1) / tpw;
     L.max_k = max_k > 0 ? max_k : 1;
@@ -87,7 +91,7 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     const int xv = input_vec(g);
     // (2^22 workgroups of sixteen waves would be 2^32 work-items)
     const int64_t n_main = ((int64_t)(B + kR * kRows - 1) / (kR * kRows)) * g.out_hcu;
-    const int waves = kR == 1 && !shape_one(v) && n_main < (1 << 22) - 2 * kCus ? kMaxWaves : 8;
+    const int waves = kR == 1 && !shape_one(v) && !pair && n_main < (1 << 22) - 2 * kCus ? kMaxWaves : 8;
     L.parts = waves / L.groups > 0 ? waves / L.groups : 1;
     // the chunk; the rows of the input panel lie 4 mod 8 words apart, so that the 16 rows x 4 units
     // of an operand read fall on different banks
@@ -104,7 +108,7 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
         L.kc = (L.max_k + 3) / 4 * 4;
         if (L.kc > kOneUnits || slots(L.kc) > most_slots || bytes(L.kc) + 4 * kOneUnits > kOneBytes) return false;
     } else {
-        const int cap = stage_bytes(kR, ps);
+        const int cap = stage_bytes(kR, pair);
         L.kc = cap / (4 * ps + x_bytes * kR * kRows) / 4 * 4;
         while (L.kc > 4 && bytes(L.kc) > cap) L.kc -= 4;
         if (L.kc < 4 || bytes(L.kc) > cap) return false;
@@ -117,6 +121,14 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     L.k_alloc = entries(L.n_chunks);
     const int steps = (L.kc + 3) / 4;                          // no share without a k-step
     if (L.parts > steps) L.parts = steps;
+    // the shares' sums, and with one row tile as many shares as leave them room behind the support
+    // tile's half in the first stage
+    const size_t vals = v == kFewOne || v == kFewChunks ? (size_t)tpw : (size_t)4 * kR * tpw;
+    const size_t tile = (size_t)kR * kRows * L.mpad * sizeof(float);
+    const size_t stage = shape_one(v) ? 16 : (size_t)stage_bytes(kR, pair);
+    auto sums_of = [&](int parts) { return (size_t)(parts - 1) * L.groups * vals * 64 * sizeof(double); };
+    if (!shape_one(v) && kR == 1)
+        while (L.parts > 1 && tile / 2 + sums_of(L.parts) > stage) --L.parts;
     L.per = (steps + L.parts - 1) / L.parts;
     L.parts = (steps + L.per - 1) / L.per;
     L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
@@ -131,7 +143,7 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     // it then holds as many chunks' as fit (546x10 inputs, 4490 units active, 1x27, 144 rows: 105
     // us; four row tiles per workgroup, whose stages leave room, 269).
     if (!shape_one(v)) {
-        const int64_t room = ((int64_t)kLdsLimit - 16 - 2 * stage_bytes(kR, ps)) / 4;
+        const int64_t room = ((int64_t)kLdsLimit / (pair ? 2 : 1) - 16 - 2 * stage_bytes(kR, pair)) / 4;
         if (kR == 1 && L.k_alloc > room) {
             L.win = room - 128 >= L.kc ? (int)((room - 128) / L.kc) : 1;
             L.k_alloc = entries(L.win);
@@ -139,16 +151,22 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     }
     const size_t table = shape_one(v) ? 0 : (size_t)L.k_alloc * 4;
     const size_t panel = shape_one(v) ? (size_t)bytes(L.kc) : 0;
-    const size_t vals = v == kFewOne || v == kFewChunks ? (size_t)tpw : (size_t)4 * kR * tpw;
-    const size_t tile = (size_t)kR * kRows * L.mpad * sizeof(float);
-    const size_t sums = (size_t)(L.parts - 1) * L.groups * vals * 64 * sizeof(double);
-    const size_t stage = shape_one(v) ? 16 : (size_t)stage_bytes(kR, ps);
+    const size_t sums = sums_of(L.parts);
     if (!shape_one(v) && tile / 2 + (kR == 1 ? sums : 0) > stage) return false;
     const size_t after = shape_one(v) ? tile + sums : kR > 1 ? sums : 0;
     *dyn_bytes = table + panel > after ? table + panel : after;
     *out = L;
     const size_t fixed = 2 * stage + (shape_one(v) ? 4 * kOneUnits : 16);
     return fixed + *dyn_bytes <= kLdsLimit;
+}
+
+// Whether more workgroups than CUs share them in pairs, each with half of the stages, so that one's
+// waits pass under the other's products.  It pays where one workgroup's waves load the SIMDs unevenly
+// or are few: hidden HCUs of seven to twelve column tiles.  1000 units, 100 MCUs, 100 HCUs at 96 rows:
+// 102 us alone, 89 in pairs; 176 MCUs, 156 units, 30 HCUs at 208 rows 33 and 29.  At six tiles a
+// workgroup alone is the faster (96 MCUs: 4%), and from thirteen (200 MCUs, 1000 units: 10%).
+inline bool two_per_cu(const Geometry& g, int64_t items) {
+    return items > kCus && g.out_mcu > 96 && g.out_mcu <= 192;
 }
 
 // The form and layout of a launch and its dynamic LDS; -1 when no form covers the sizes.  ops:
@@ -166,6 +184,7 @@ inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, 
     }
     if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
     take(kOneChunk);
+    if (two_per_cu(g, row_tiles * g.out_hcu)) take(kTwoPerCu);
     take(kChunks);
     return shape;
 }

@@ -38,6 +38,12 @@ SHAPES = [
     # chunks: a partial last one, unit counts one past a chunk, every panel stride
     (300, 3, 2, 70, 201, 40), (700, 1, 3, 6, 613, 18), (600, 2, 2, 100, 599, 20),
     (200, 2, 2, 129, 151, 17), (150, 3, 2, 257, 99, 16), (100, 2, 2, 513, 61, 18),
+    # wide hidden HCUs: whole and partial k-steps at the end, shares that leave no room for their sums
+    (160, 3, 2, 200, 133, 20), (90, 2, 2, 256, 78, 33), (200, 2, 1, 300, 190, 19), (120, 2, 3, 400, 99, 2),
+    (100, 1, 2, 512, 77, 17), (60, 3, 1, 700, 47, 18), (40, 2, 2, 1024, 30, 16), (50, 1, 1, 1000, 45, 1),
+    # two workgroups per CU: partial chunks and k-steps, a unit table in parts
+    (200, 2, 90, 100, 120, 48), (500, 1, 300, 113, 389, 2), (200, 3, 64, 160, 133, 80),
+    (900, 2, 60, 150, 850, 70), (820, 2, 29, 97, 811, 144),
     # many rows: groups of four row tiles, the last one partial
     (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
     # a readout, row by row: weight rows of 16, 8 and 4 bytes, ragged batches
