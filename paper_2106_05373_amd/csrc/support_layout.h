@@ -10,11 +10,10 @@ namespace bcpnn {
 
 constexpr int kRows = 16;          // batch rows per row tile
 constexpr int kMaxWaves = 16;
-// (row tile, hidden HCU) items from which kR = 4 pays: its workgroups, a quarter of the items, have
-// to fill the CUs (8192 rows x 30 HCUs, 15360 items: 270 us against 430 with kR = 2)
-constexpr int64_t kManyRowTiles = 1024;
 constexpr int kCus = 256;                 // compute units
 constexpr int64_t kL2Bytes = 32 << 20;    // of all XCDs
+constexpr int kXcds = 8;
+constexpr int kFewUnits = 16;             // with so few units a launch costs its workgroups, not its work
 constexpr int kMinSplit = 16;             // least workgroups for the input's split
 constexpr int kOneUnits = 1024;           // unit table of the one-chunk variants
 constexpr int kOneBytes = 120 * 1024;     // their panels and table
@@ -176,11 +175,52 @@ inline bool two_per_cu(const Geometry& g, int64_t items) {
     return items > kCus && g.out_mcu > 96 && g.out_mcu <= 192;
 }
 
+// Time of a launch of more (row tile, hidden HCU) items than CUs, for the choice among its forms, as the
+// rounds of workgroups that the CUs run one after another, each weighed with what it takes per row
+// tile; the unit is a row tile of four, two workgroups to a CU.  What tells the forms apart: a group of
+// row tiles costs four, dead ones too; a last round costs a whole one (less where every CU has one
+// workgroup of it); a workgroup alone on its CU waits for its first chunk and at its end, which many
+// units outweigh; and its waves may fill the SIMDs better (five column tiles: fifteen waves of a third of
+// the k-steps each, with four row tiles five waves).  The weights are fitted to 1046 sizes and tried on
+// 2500 (30 to 3000 HCUs, 2 to 128 MCUs, 3 to 3000 units, 2 to 4096 rows).  Against four row tiles from
+// 1024 items on, whatever their rows, 17% faster on average: 1100 HCUs x 10 MCUs, 1000 units, 16 rows 157
+// -> 62 us; 210 x 100, 80 rows 195 -> 142; 30 x 100 of 156 units, 512 rows 33 -> 26.
+inline double launch_cost(const Geometry& g, int32_t B, const SupportLayout& L, int v, size_t lds) {
+    const int full = L.n_main / (2 * kCus), rest = L.n_main % (2 * kCus);
+    const double rounds = (L.n_main + kCus - 1) / kCus;          // one workgroup to a CU
+    const double K = L.max_k;
+    switch (v) {
+        case kManyRows: {
+            const bool shared = 2 * (2 * stage_bytes(kManyTiles, false) + 16 + lds) <= kLdsLimit;
+            if (!shared) return 5.2 * rounds;
+            return 8.0 * full + (rest == 0 ? 0.0 : rest <= kCus ? 5.2 : 8.0);
+        }
+        case kTwoPerCu:
+            return 1.25 * (2.0 * full + (rest == 0 ? 0.0 : rest <= kCus ? 1.46 : 2.0));
+        case kOneChunk:
+            // panels that leave a CU a single workgroup; smaller ones, whose workgroups share it, where
+            // an XCD's L2 holds the inputs that they gather
+            if (2 * (4 * (size_t)kOneUnits + 32 + lds) > kLdsLimit) return 1.7 * rounds;
+            if (L.n_tiles > 4) return 1.45 * rounds;
+            return rounds * ((int64_t)B * g.n_in * 4 > kL2Bytes / kXcds ? 1.4 : 1.25);
+        default: {
+            // waves on the fullest SIMD per share of the k-steps
+            const int many = 8 / L.n_tiles > 0 ? 8 / L.n_tiles : 1;
+            const double here = (double)((L.groups * L.parts + 3) / 4) / L.parts;
+            const double there = (double)((L.n_tiles * many + 3) / 4) / many;
+            const double fill = L.n_tiles <= 8 ? 0.6 + 0.4 * here / there : 1.0;
+            const double alone = (K + 300.0) / (0.85 * K + 30.0);
+            return rounds * fill * (alone < 2.0 ? alone : 2.0);
+        }
+    }
+}
+
 // The form and layout of a launch and its dynamic LDS; -1 when no form covers the sizes.  ops:
-// training.
+// training.  One chunk where the units fit, else several; with more items than CUs another form where it
+// costs less.
 inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, SupportLayout* lay,
                          size_t* lds) {
-    const int64_t row_tiles = ((int64_t)B + kRows - 1) / kRows;
+    const int64_t items = ((int64_t)B + kRows - 1) / kRows * g.out_hcu;
     int shape = -1;
     auto take = [&](int v) {
         if (shape < 0 && make_layout(g, B, max_k, v, lay, lds)) shape = v;
@@ -189,10 +229,28 @@ inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, 
         take(kFewOne);
         take(kFewChunks);
     }
-    if (row_tiles * g.out_hcu >= kManyRowTiles) take(kManyRows);
     take(kOneChunk);
-    if (two_per_cu(g, row_tiles * g.out_hcu)) take(kTwoPerCu);
+    if (two_per_cu(g, items)) take(kTwoPerCu);
     take(kChunks);
+    if (items <= kCus || shape == kFewOne || shape == kFewChunks) return shape;
+    double least = shape < 0 ? 0.0 : launch_cost(g, B, *lay, shape, *lds);
+    auto consider = [&](int v) {
+        SupportLayout L;
+        size_t bytes = 0;
+        if (!make_layout(g, B, max_k, v, &L, &bytes)) return;
+        const double cost = launch_cost(g, B, L, v, bytes);
+        if (shape >= 0 && cost >= least) return;
+        shape = v;
+        least = cost;
+        *lay = L;
+        *lds = bytes;
+    };
+    if (two_per_cu(g, items) && shape == kOneChunk &&
+        2 * (4 * (size_t)kOneUnits + 32 + *lds) > kLdsLimit)
+        consider(kTwoPerCu);
+    if (shape != kOneChunk && max_k <= kFewUnits) least = 1e30;   // (one such workgroup fills a CU's LDS)
+    // (one or two row tiles of four: never for their work)
+    if (items > 2 * (int64_t)g.out_hcu || least == 1e30) consider(kManyRows);
     return shape;
 }
 

@@ -57,6 +57,8 @@ static void check(const Geometry& g, int32_t B, int32_t max_k, bool ops) {
     // a wide hidden HCU's stages take what the launch has: shorter chunks end and drain more often
     if (!one && kR == 1 && L.n_chunks > 1)
         CHECK(panel + 4 * (4 * stride + 4 * kRows) + 512 > (pair ? 36 : 72) * 1024, "part of the LDS idle");
+    // row tiles past the batch, which a group computes like the others
+    CHECK(5 * L.n_row_groups * kR <= 8 * L.n_row_tiles || max_k <= kFewUnits, "matrix work of absent rows");
     // weights are not read again for every row tile of a batch that the L2s hold
     if (kR == 1 && (int64_t)B * g.n_in * 4 <= kL2Bytes) CHECK(!L.row_major, "order");
     if (pair) CHECK(2 * (2 * stage + 16 + lds) <= kLdsLimit && L.n_main > kCus, "two workgroups per CU");

@@ -44,6 +44,9 @@ SHAPES = [
     # two workgroups per CU: partial chunks and k-steps, a unit table in parts
     (200, 2, 90, 100, 120, 48), (500, 1, 300, 113, 389, 2), (200, 3, 64, 160, 133, 80),
     (900, 2, 60, 150, 850, 70), (820, 2, 29, 97, 811, 144),
+    # many hidden HCUs with one, two and five row tiles, a group's last ones absent; a handful of units
+    (30, 1, 1100, 10, 25, 16), (30, 1, 1100, 10, 25, 17), (60, 2, 210, 100, 50, 80), (40, 2, 520, 20, 30, 33),
+    (200, 3, 110, 30, 133, 72), (450, 1, 260, 12, 401, 40), (12, 1, 3000, 2, 3, 2), (700, 2, 70, 100, 350, 71),
     # many rows: groups of four row tiles, the last one partial
     (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
     # a readout, row by row: weight rows of 16, 8 and 4 bytes, ragged batches
