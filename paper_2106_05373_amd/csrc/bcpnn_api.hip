@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "bcpnn_internal.h"
+#include "support_layout.h"
 
 using bcpnn::Geometry;
 
@@ -738,10 +739,8 @@ bcpnn_status bcpnn_predict(bcpnn_layer* hidden, bcpnn_layer* readout, const floa
         return fail(BCPNN_EINVAL, "the readout must have one HCU over the hidden units, on one stream");
     if (B < 1 || rows < 1) return fail(BCPNN_EINVAL, "B and rows must be positive");
     // Rows per launch, even over the launches: whole row tiles, or as few as keep x 16-byte aligned,
-    // within the limits of a launch: 32-bit byte offsets into its inputs and 2^23 workgroups.
-    const int64_t widest = std::max(gh.n_in, gr.n_in);
-    const int64_t most = std::min((int64_t)(UINT32_MAX / 4) / widest, ((int64_t)1 << 27) / gh.out_hcu);
-    int64_t step = std::min<int64_t>({rows, B, most / 16 * 16});
+    // within the limits of a launch.
+    int64_t step = std::min<int64_t>({rows, B, bcpnn::most_rows(gh), bcpnn::most_rows(gr)});
     if (step < B) {
         const int64_t unit = step >= 16 ? 16 : gh.n_in % 4 == 0 ? 1 : gh.n_in % 2 == 0 ? 2 : 4;
         step = step / unit * unit;

@@ -72,9 +72,35 @@ inline uint32_t magic_of(int d) { return (uint32_t)(((1ull << 32) + (uint64_t)d 
 
 inline int input_vec(const Geometry& g) { return g.in_mcu % 2 == 0 ? 2 : 1; }
 
+// Workgroups of a training launch that split the input, beside the support's n_main: a wave per
+// task, or on the CUs that the support leaves idle.
+inline int64_t split_workgroups(const Geometry& g, const SupportLayout& lay) {
+    const int n_waves = lay.groups * lay.parts;
+    int64_t n_split = ((int64_t)lay.n_row_tiles * ((g.n_in + 63) / 64) + n_waves - 1) / n_waves;
+    if (lay.n_main < kCus && n_split > kCus - lay.n_main)
+        n_split = kCus - lay.n_main > kMinSplit ? kCus - lay.n_main : n_split < kMinSplit ? n_split : kMinSplit;
+    return n_split;
+}
+
+// Whether a launch of this layout keeps below 2^32 work-items (what a grid can have).
+inline bool launchable(const Geometry& g, const SupportLayout& lay, bool ops) {
+    const int64_t workgroups = lay.n_main + (ops ? split_workgroups(g, lay) : 0);
+    return workgroups * lay.groups * lay.parts * 64 < (int64_t)1 << 32;
+}
+
+// The most rows of one launch: its inputs have 32-bit byte offsets, and its row tiles x hidden HCUs
+// workgroups keep below 2^32 work-items with the waves that the columns need (eight, sixteen above 128
+// MCUs).  Layers of more rows than that do not fit the device's memory; a prediction's launches, which
+// no batch size bounds, are cut to it.
+inline int64_t most_rows(const Geometry& g) {
+    const int64_t by_inputs = (int64_t)(UINT32_MAX / 4) / g.n_in;
+    const int64_t by_items = (((int64_t)1 << (g.out_mcu > 128 ? 26 : 27)) - 1) / g.out_hcu;
+    return (by_inputs < by_items ? by_inputs : by_items) / kRows * kRows;
+}
+
 // Layout of a launch in one shape and its dynamic LDS, or false when the shape does not cover the
-// sizes.
-inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, SupportLayout* out,
+// sizes.  ops: training.
+inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, bool ops, SupportLayout* out,
                         size_t* dyn_bytes) {
     SupportLayout L{};
     const int kR = shape_rows(v), ps = panel_stride(g.out_mcu);
@@ -89,9 +115,11 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     L.vec4 = g.out_mcu % 4 == 0 && g.n_out % 4 == 0;
     L.mpad = (g.out_mcu + 15) / 16 * 16 + 4;
     const int xv = input_vec(g);
-    // (2^22 workgroups of sixteen waves would be 2^32 work-items)
     const int64_t n_main = ((int64_t)(B + kR * kRows - 1) / (kR * kRows)) * g.out_hcu;
-    const int waves = kR == 1 && !shape_one(v) && !pair && n_main < (1 << 22) - 2 * kCus ? kMaxWaves : 8;
+    if (n_main > INT32_MAX / 2) return false;
+    L.n_main = (int)n_main;
+    L.n_row_tiles = (B + kRows - 1) / kRows;
+    const int waves = kR == 1 && !shape_one(v) && !pair ? kMaxWaves : 8;
     L.parts = waves / L.groups > 0 ? waves / L.groups : 1;
     // the chunk; the rows of the input panel lie 4 mod 8 words apart, so that the 16 rows x 4 units
     // of an operand read fall on different banks
@@ -129,12 +157,13 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     auto sums_of = [&](int parts) { return (size_t)(parts - 1) * L.groups * vals * 64 * sizeof(double); };
     if (!shape_one(v) && kR == 1)
         while (L.parts > 1 && tile / 2 + sums_of(L.parts) > stage) --L.parts;
+    while (L.parts > 1 && !launchable(g, L, ops)) --L.parts;
+    if (!launchable(g, L, ops)) return false;
     L.per = (steps + L.parts - 1) / L.parts;
     L.parts = (steps + L.per - 1) / L.per;
     L.rw = (kR * kRows + L.groups * L.parts - 1) / (L.groups * L.parts);
     L.x_slots = slots(L.kc);
     if (shape_one(v) && L.x_slots > most_slots) return false;
-    L.n_row_tiles = (B + kRows - 1) / kRows;
     L.n_row_groups = (L.n_row_tiles + kR - 1) / kR;
     // The row tiles of a hidden HCU one after another: its weights then stay in an XCD's L2, and so do
     // the inputs that every hidden HCU gathers again.  A batch beyond the L2s (32 MiB) and larger than
@@ -143,8 +172,6 @@ inline bool make_layout(const Geometry& g, int32_t B, int32_t max_k, int v, Supp
     // rows the other way, 305 against 539 us.)  Four row tiles share their weights as it is.
     const int64_t x_bytes_all = (int64_t)B * g.n_in * 4, w_bytes = (int64_t)L.max_k * g.n_out * 4;
     L.row_major = kR > 1 || (!shape_one(v) && x_bytes_all > kL2Bytes && x_bytes_all > w_bytes);
-    if (n_main > INT32_MAX / 2) return false;
-    L.n_main = (int)n_main;
     // A table of every unit may leave no room for the stages (with one row tile, above 3500 units):
     // it then holds as many chunks' as fit (546x10 inputs, 4490 units active, 1x27, 144 rows: 105
     // us; four row tiles per workgroup, whose stages leave room, 269).
@@ -223,7 +250,7 @@ inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, 
     const int64_t items = ((int64_t)B + kRows - 1) / kRows * g.out_hcu;
     int shape = -1;
     auto take = [&](int v) {
-        if (shape < 0 && make_layout(g, B, max_k, v, lay, lds)) shape = v;
+        if (shape < 0 && make_layout(g, B, max_k, v, ops, lay, lds)) shape = v;
     };
     if (!ops && B == 1) {
         take(kFewOne);
@@ -237,7 +264,7 @@ inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, 
     auto consider = [&](int v) {
         SupportLayout L;
         size_t bytes = 0;
-        if (!make_layout(g, B, max_k, v, &L, &bytes)) return;
+        if (!make_layout(g, B, max_k, v, ops, &L, &bytes)) return;
         const double cost = launch_cost(g, B, L, v, bytes);
         if (shape >= 0 && cost >= least) return;
         shape = v;
@@ -252,16 +279,6 @@ inline int choose_layout(const Geometry& g, int32_t B, int32_t max_k, bool ops, 
     // (one or two row tiles of four: never for their work)
     if (items > 2 * (int64_t)g.out_hcu || least == 1e30) consider(kManyRows);
     return shape;
-}
-
-// Workgroups of a training launch that split the input, beside the support's n_main: a wave per
-// task, or on the CUs that the support leaves idle.
-inline int64_t split_workgroups(const Geometry& g, const SupportLayout& lay) {
-    const int n_waves = lay.groups * lay.parts;
-    int64_t n_split = ((int64_t)lay.n_row_tiles * ((g.n_in + 63) / 64) + n_waves - 1) / n_waves;
-    if (lay.n_main < kCus && n_split > kCus - lay.n_main)
-        n_split = kCus - lay.n_main > kMinSplit ? kCus - lay.n_main : n_split < kMinSplit ? n_split : kMinSplit;
-    return n_split;
 }
 
 }  // namespace bcpnn

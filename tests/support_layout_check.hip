@@ -49,6 +49,8 @@ static void check(const Geometry& g, int32_t B, int32_t max_k, bool ops) {
     if (one) CHECK(tile + sums <= lds, "tile");
     else if (kR == 1) CHECK(tile / 2 + sums <= stage, "tile");
     else CHECK(tile / 2 <= stage && sums <= lds, "tile");
+    const int64_t split = ops ? split_workgroups(g, L) : 0;
+    CHECK(((int64_t)L.n_main + split) * 64 * waves < (int64_t)1 << 32, "2^32 work-items");
     // rows: every row tile in a workgroup
     CHECK(L.n_row_tiles == (B + kRows - 1) / kRows && L.n_row_groups * kR >= L.n_row_tiles &&
               (L.n_row_groups - 1) * kR < L.n_row_tiles && L.n_main == L.n_row_groups * g.out_hcu,
@@ -82,6 +84,22 @@ int main() {
                         const Geometry g{in_hcu + 5, in_mcu, h, m, (int64_t)(in_hcu + 5) * in_mcu, (int64_t)h * m};
                         for (bool ops : {false, true}) check(g, b, in_hcu * in_mcu, ops);
                     }
+    // the largest layers, and as many rows as a launch takes or a layer's training operands (96 bytes
+    // per row and hidden unit) leave room for on the device
+    for (int m : mcus)
+        for (int k : {4, 156, 399, 12288})
+            for (int h : {(1 << 22) / m, (1 << 21) / m, (1 << 16) / m}) {
+                if (h < 1) continue;
+                const Geometry g{k + 5, 1, h, m, k + 5, (int64_t)h * m};
+                const int64_t most = most_rows(g);
+                const int64_t layer = (int64_t)288e9 / 96 / g.n_out;
+                for (int64_t b : {most, most - 15, most / 3}) {
+                    if (b < 1) continue;
+                    check(g, (int32_t)b, k, false);
+                    const int64_t t = b < layer ? b : layer;
+                    if (t > 0 && (t + 15) / 16 * h <= 1 << 23) check(g, (int32_t)t, k, true);
+                }
+            }
     printf("%d failures\n", failures);
     return failures != 0;
 }
