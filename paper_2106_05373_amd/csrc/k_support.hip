@@ -205,14 +205,14 @@ constexpr int kThinRows = 1024;           // up to so many rows
 constexpr int kThinThreads = 512;
 constexpr int kThinColumns = 16;
 
-// The last step of the row-by-row kernels, by 16 lanes: column tid of `row` of hidden HCU hj has the
-// sum v; its support, then the softmax or argmax.
-__device__ __forceinline__ void thin_finish(const Geometry& g, int row, int hj, int tid, double v,
-                                            float bias, float gain, int mode, float* y, float* s,
+// The last step of the row-by-row kernels, by 16 lanes: column tid of `row` has the sum v; its support,
+// then the softmax or argmax.
+__device__ __forceinline__ void thin_finish(const Geometry& g, int row, int tid, double v, float bias,
+                                            float gain, int mode, float* y, float* s,
                                             int32_t* winner) {
     const int M = g.out_mcu;
     const bool in = tid < M;
-    const int64_t o = (int64_t)row * g.n_out + (int64_t)hj * M + tid;
+    const int64_t o = (int64_t)row * M + tid;
     const float sv = (float)(v + (double)bias);
     if (s && in) s[o] = sv;
     if (mode == 0) {
@@ -230,18 +230,18 @@ __device__ __forceinline__ void thin_finish(const Geometry& g, int row, int hj, 
             const int oi = __shfl_xor(bi, off, 64);
             if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
         }
-        if (tid == 0) winner[(int64_t)row * g.out_hcu + hj] = bi;
+        if (tid == 0) winner[row] = bi;
     }
 }
 
-// A narrow hidden HCU with many active units and a small batch (a readout: 3000 units to 10
+// A single narrow hidden HCU with many active units and a small batch (a readout: 3000 units to 10
 // classes, 128 rows): by row tiles it would fill a handful of CUs, each with a long chain of
 // chunks.  Here a workgroup takes one row: a thread accumulates all M_out (<= 16) columns of its
 // units k, k + 512, ... with fp64 FMAs (W: floats per weight load), the waves add their lanes by
 // halving exchanges (after which lanes hold single columns), and 16 lanes add the waves in order,
 // then take the softmax or argmax.  Nothing waits between the loads and the reduction, and the
-// weights are read by every workgroup from L2.  Measured at 128 rows,
-// 3000 -> 10: 11 us (in chunks of units, 8 workgroups: 25 us; one column tile per wave: 87 us).
+// weights are read by every workgroup from L2.  Measured at 128 rows, 2900 of 3000 units -> 10:
+// THIN_US us (in chunks of units, 8 workgroups: CHUNK_US us).
 template <int W>
 __global__ void __launch_bounds__(kThinThreads)
 support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __restrict__ w,
@@ -251,12 +251,9 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
     typedef float wvec __attribute__((ext_vector_type(W)));
     __shared__ double sums[kThinThreads / 64][kThinColumns];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int hj = blockIdx.x % g.out_hcu;
-    const int row = blockIdx.x / g.out_hcu;
+    const int row = blockIdx.x;
     const int M = g.out_mcu;
-    const int32_t k_total = act_count[hj] * g.in_mcu;
-    const int32_t* alist = act_list + (int64_t)hj * g.in_hcu;
-    const float* wb = w + (int64_t)hj * M;
+    const int32_t k_total = act_count[0] * g.in_mcu;
     const float* xrow = x + (int64_t)row * g.n_in;
     double acc[kThinColumns];
 #pragma unroll
@@ -267,9 +264,9 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
         int32_t u = k;
         if (!full) {
             const int32_t h = mcu_magic ? (int32_t)__umulhi((uint32_t)k, mcu_magic) : k;
-            u = (alist[h] - h) * g.in_mcu + k;
+            u = (act_list[h] - h) * g.in_mcu + k;
         }
-        const float* wr = wb + (int64_t)u * g.n_out;
+        const float* wr = w + (int64_t)u * M;
         wvec wv[kThinColumns / W];
 #pragma unroll
         for (int q = 0; q < kThinColumns / W; ++q) {
@@ -304,7 +301,7 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < kThinThreads / 64; ++q) v += sums[q][tid];
-    thin_finish(g, row, hj, tid, v, bias[(int64_t)hj * M + (tid < M ? tid : 0)], gain, mode, y, s, winner);
+    thin_finish(g, row, tid, v, bias[tid < M ? tid : 0], gain, mode, y, s, winner);
 }
 
 // The same for a layer whose single hidden HCU sees every input unit (M_out of 4 to 16): its weights
@@ -386,11 +383,11 @@ support_flat_kernel(Geometry g, const float* __restrict__ x, const float* __rest
     const int rest = n_in * M - 4 * n_vec;                     // columns M - rest .. of the last unit
     if (tid < M && tid >= M - rest)
         v = fma((double)xrow[n_in - 1], (double)w[(int64_t)(n_in - 1) * M + tid], v);
-    thin_finish(g, row, 0, tid, v, bias_c, gain, mode, y, s, winner);
+    thin_finish(g, row, tid, v, bias_c, gain, mode, y, s, winner);
 }
 
-// kR: row tiles per workgroup.  kV: input elements per load (2 when input HCUs have an even number
-// of MCUs).  kS: row stride of the weight panel in LDS (panel_stride).
+// kR: row tiles per workgroup.  kV: input elements per load of the one-chunk forms (2 when input HCUs
+// have an even number of MCUs).  kS: row stride of the weight panel in LDS (panel_stride).
 // kMulti: several chunks (else the one chunk holds every active unit).  kFew: a single row, on
 // fp64 FMAs.  kOps: training (the contraction operands are written).  kStamp: the launch stamps
 // its start and end (training launches that profiling times).  kPair: stages of half the size, so that
@@ -922,41 +919,42 @@ support_kernel(Geometry g, SupportLayout lay, const float* __restrict__ x, int32
     }
 }
 
-// Calls f with the kernel of a shape, panel stride and input vector.
+// Calls f with the kernel of a shape, panel stride and input vector (which the one-chunk forms gather
+// with: the others have a vector of 1).
 template <bool kOps, bool kStamp, typename F>
 hipError_t with_kernel(int shape, int stride, int xv, F&& f) {
-    auto narrow = [&](auto s_c, auto v_c) -> hipError_t {
-        constexpr int S = decltype(s_c)::value, V = decltype(v_c)::value;
+    auto narrow = [&](auto s_c) -> hipError_t {
+        constexpr int S = decltype(s_c)::value;
         switch (shape) {
-            case kOneChunk: return f(support_kernel<1, S, V, false, false, kOps, kStamp>);
-            case kChunks: return f(support_kernel<1, S, V, true, false, kOps, kStamp>);
-            case kManyRows: return f(support_kernel<kManyTiles, S, V, true, false, kOps, kStamp>);
+            case kOneChunk:
+                return xv == 2 ? f(support_kernel<1, S, 2, false, false, kOps, kStamp>)
+                               : f(support_kernel<1, S, 1, false, false, kOps, kStamp>);
+            case kChunks: return f(support_kernel<1, S, 1, true, false, kOps, kStamp>);
+            case kManyRows: return f(support_kernel<kManyTiles, S, 1, true, false, kOps, kStamp>);
             case kTwoPerCu:
-                if constexpr (S == 128) return f(support_kernel<1, S, V, true, false, kOps, kStamp, true>);
+                if constexpr (S == 128) return f(support_kernel<1, S, 1, true, false, kOps, kStamp, true>);
                 break;
             default: break;
         }
         if constexpr (!kOps) {
-            if (shape == kFewOne) return f(support_kernel<1, S, V, false, true, false, false>);
-            if (shape == kFewChunks) return f(support_kernel<1, S, V, true, true, false, false>);
+            if (shape == kFewOne)
+                return xv == 2 ? f(support_kernel<1, S, 2, false, true, false, false>)
+                               : f(support_kernel<1, S, 1, false, true, false, false>);
+            if (shape == kFewChunks) return f(support_kernel<1, S, 1, true, true, false, false>);
         }
         return hipErrorInvalidValue;
     };
-    auto with_stride = [&](auto v_c) -> hipError_t {
-        constexpr int V = decltype(v_c)::value;
-        switch (stride) {
-            case 16: return narrow(Count<16>{}, v_c);
-            case 80: return narrow(Count<80>{}, v_c);
-            case 128: return narrow(Count<128>{}, v_c);
-            case 256:
-                return shape == kTwoPerCu ? f(support_kernel<1, 256, V, true, false, kOps, kStamp, true>)
-                                          : f(support_kernel<1, 256, V, true, false, kOps, kStamp>);
-            case 512: return f(support_kernel<1, 512, V, true, false, kOps, kStamp>);
-            case 1024: return f(support_kernel<1, 1024, V, true, false, kOps, kStamp>);
-            default: return hipErrorInvalidValue;
-        }
-    };
-    return xv == 2 ? with_stride(Count<2>{}) : with_stride(Count<1>{});
+    switch (stride) {
+        case 16: return narrow(Count<16>{});
+        case 80: return narrow(Count<80>{});
+        case 128: return narrow(Count<128>{});
+        case 256:
+            return shape == kTwoPerCu ? f(support_kernel<1, 256, 1, true, false, kOps, kStamp, true>)
+                                      : f(support_kernel<1, 256, 1, true, false, kOps, kStamp>);
+        case 512: return f(support_kernel<1, 512, 1, true, false, kOps, kStamp>);
+        case 1024: return f(support_kernel<1, 1024, 1, true, false, kOps, kStamp>);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // Order of the input's column sums.
@@ -1000,8 +998,7 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
     }
     if (!ops && g.out_mcu <= kThinColumns && max_k >= kThinUnits &&
         g.out_hcu == 1 && B <= kThinRows) {
-        const int width = g.out_mcu % 4 == 0 && g.n_out % 4 == 0 ? 4
-                          : g.out_mcu % 2 == 0 && g.n_out % 2 == 0 ? 2 : 1;
+        const int width = g.out_mcu % 4 == 0 ? 4 : g.out_mcu % 2 == 0 ? 2 : 1;
         const uint32_t magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
         // every input unit active (a single hidden HCU: its count is max_active) and no more than two
         // units in four consecutive weights: the contiguous form, 6.4 against 11.8 us (3000 -> 10)
@@ -1014,7 +1011,7 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
         }
         return launch_timed(width == 4 ? support_thin_kernel<4>
                             : width == 2 ? support_thin_kernel<2> : support_thin_kernel<1>,
-                            dim3((unsigned)(B * g.out_hcu)), dim3(kThinThreads), 0, stream, start, stop,
+                            dim3((unsigned)B), dim3(kThinThreads), 0, stream, start, stop,
                             g, x, w, bias, act_list, act_count, magic, gain, mode, y, s, winner);
     }
     SupportLayout lay;
