@@ -240,8 +240,8 @@ __device__ __forceinline__ void thin_finish(const Geometry& g, int row, int tid,
 // units k, k + 512, ... with fp64 FMAs (W: floats per weight load), the waves add their lanes by
 // halving exchanges (after which lanes hold single columns), and 16 lanes add the waves in order,
 // then take the softmax or argmax.  Nothing waits between the loads and the reduction, and the
-// weights are read by every workgroup from L2.  Measured at 128 rows, 2900 of 3000 units -> 10:
-// THIN_US us (in chunks of units, 8 workgroups: CHUNK_US us).
+// weights are read by every workgroup from L2.  128 rows, 2900 of 3000 units -> 10: 12.3 us (in chunks of
+// units, 8 workgroups: 27).
 template <int W>
 __global__ void __launch_bounds__(kThinThreads)
 support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __restrict__ w,
@@ -311,8 +311,8 @@ support_thin_kernel(Geometry g, const float* __restrict__ x, const float* __rest
 // threads' sums are [4 T / M][M] in LDS, added up by 32 lanes per column.  Elements past the last
 // whole vector belong to the last unit and are added at the end.  Bound by its instructions and its
 // round trips of memory, so there is no division, an input is converted once, and the LDS reads of
-// the sum go out together.  128 rows, 3000 -> 10: 6.4 us; with divisions, a conversion per product
-// and the sum in a loop 10.6; the kernel above 11.8.
+// the sum go out together.  128 rows, 3000 -> 10: 6.3 us; with divisions, a conversion per product
+// and the sum in a loop 10.6; the kernel above 11.3.
 template <int kBatch>
 __device__ __forceinline__ void flat_passes(const float* __restrict__ xrow, const f4* __restrict__ w4,
                                             int n_vec, int n_pass, int T, int U, int M, int n_in,
@@ -1001,7 +1001,7 @@ hipError_t launch_support(hipStream_t stream, const Geometry& g, const float* x,
         const int width = g.out_mcu % 4 == 0 ? 4 : g.out_mcu % 2 == 0 ? 2 : 1;
         const uint32_t magic = g.in_mcu > 1 ? magic_of(g.in_mcu) : 0;
         // every input unit active (a single hidden HCU: its count is max_active) and no more than two
-        // units in four consecutive weights: the contiguous form, 6.4 against 11.8 us (3000 -> 10)
+        // units in four consecutive weights: the contiguous form, 6.3 against 11.3 us (3000 -> 10)
         if (max_active == g.in_hcu && g.out_mcu >= 4) {
             const int whole = g.out_mcu % 4 == 0 ? g.out_mcu / 4 : g.out_mcu % 2 == 0 ? g.out_mcu / 2 : g.out_mcu;
             const int T = kThinThreads / whole * whole;
