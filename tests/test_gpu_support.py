@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2106_05373_amd import synth
-from pairs import TOL_ACT, Pair, assert_support_close, gpu_config, max_abs
+from pairs import TOL_ACT, Pair, assert_state_close, assert_support_close, gpu_config, max_abs
 
 pytestmark = pytest.mark.gpu
 
@@ -47,7 +47,10 @@ SHAPES = [
     # many hidden HCUs with one, two and five row tiles, a group's last ones absent; a handful of units
     (30, 1, 1100, 10, 25, 16), (30, 1, 1100, 10, 25, 17), (60, 2, 210, 100, 50, 80), (40, 2, 520, 20, 30, 33),
     (200, 3, 110, 30, 133, 72), (450, 1, 260, 12, 401, 40), (12, 1, 3000, 2, 3, 2), (700, 2, 70, 100, 350, 71),
-    # many rows: groups of four row tiles, the last one partial
+    # many rows: groups of four row tiles, the last one with 17 rows (weight rows of 4, 8 and 16 bytes)
+    (200, 3, 60, 10, 133, 337), (200, 3, 60, 21, 133, 337), (200, 3, 40, 81, 133, 337),
+    (160, 2, 80, 100, 150, 337), (90, 2, 60, 128, 78, 465),
+    # ... of few units: several one-chunk workgroups per CU instead
     (60, 2, 40, 20, 15, 450), (90, 2, 30, 100, 39, 600), (64, 3, 130, 10, 21, 140),
     # a readout, row by row: weight rows of 16, 8 and 4 bytes, ragged batches
     (30, 100, 1, 16, 30, 40), (30, 100, 1, 10, 30, 128), (50, 13, 1, 7, 49, 19), (600, 1, 1, 2, 513, 1),
@@ -99,6 +102,46 @@ def test_training_batch_of_more_units_than_the_table_holds():
     got, want = pair.gpu.get_state(), pair.ora.get_state()
     for key in ("pi", "pj", "pij"):
         assert max_abs(got[key], want[key]) <= TOL_ACT, key
+    pair.close()
+
+
+# (in_hcu, in_mcu, out_hcu, out_mcu, active input HCUs, batch, pairs)
+TRAINED = [
+    # four row tiles per workgroup, the last group one full row tile and a row of the next: shares of the
+    # k-steps and none, weight rows of 4, 8 and 16 bytes
+    (200, 3, 60, 10, 133, 337, 0), (300, 2, 70, 10, 200, 337, 1), (200, 3, 60, 21, 133, 337, 0),
+    (200, 3, 40, 81, 133, 337, 0), (160, 2, 80, 100, 150, 337, 1), (200, 3, 48, 40, 133, 320, 0),
+    # two workgroups per CU; wide hidden HCUs
+    (200, 3, 30, 100, 133, 150, 0), (200, 3, 26, 160, 133, 150, 0), (150, 2, 17, 300, 90, 260, 1),
+    # one row tile of many hidden HCUs
+    (200, 2, 1100, 10, 150, 3, 1),
+]
+
+
+@pytest.mark.parametrize("target", [False, True], ids=["unsupervised", "target"])
+@pytest.mark.parametrize("shape", TRAINED, ids=lambda s: "x".join(map(str, s)))
+def test_training_batches_match_oracle(shape, target):
+    """Two batches in the forms of many row tiles: the activities and the state, with the activity and
+    with a target in the traces."""
+    hin, min_, hout, mout, k, B, pairs = shape
+    rng = np.random.default_rng(hout * 3 + mout)
+    mask = np.stack([synth.random_mask(hin, 1, k, 70 + c)[:, 0] for c in range(hout)], 1)
+    pair = Pair(gpu_config(hin, min_, hout, mout, B, alpha=0.05, complement_pairs=pairs), mask)
+    pair.ora.set_state(given_state(rng, hin, min_, hout, mout, mask))
+    pair.sync_gpu_to_oracle()
+    for _ in range(2):
+        if pairs:
+            x = synth.encode_pixels(rng.random((B, hin)).astype(np.float32))
+        else:
+            p = rng.random((B, hin, min_)) + 0.05
+            x = (p / p.sum(-1, keepdims=True)).reshape(B, -1).astype(np.float32)
+        t = None
+        if target:
+            t = np.concatenate([synth.one_hot(rng.integers(0, mout, B), mout) for _ in range(hout)], 1)
+        y, y_o, _ = pair.train(x, t)
+        assert max_abs(y, y_o) <= TOL_ACT
+        assert_state_close(pair.gpu.get_state(), pair.ora.get_state())
+        pair.sync_gpu_to_oracle()
     pair.close()
 
 
