@@ -93,7 +93,7 @@ def kernel_digest(csrc, files):
 
 SWEEP_SOURCES = ("k_trace.hip", "bcpnn_internal.h", "device_common.h")
 WEIGHT_SOURCES = ("k_weights.hip", "bcpnn_internal.h", "device_common.h")
-SUPPORT_SOURCES = ("k_support.hip", "bcpnn_internal.h", "device_common.h")
+SUPPORT_SOURCES = ("k_support.hip", "support_layout.h", "bcpnn_internal.h", "device_common.h")
 
 
 def sweep_sizes(sched, first, last):

@@ -149,7 +149,10 @@ bcpnn_status bcpnn_layer_create(const bcpnn_config *cfg, const uint8_t *mask_hos
 void bcpnn_layer_destroy(bcpnn_layer *layer);
 
 /* Inference (Alg. 1 support and softmax lines, no learning): y_dev [B][N_out] receives the
- * activities; s_dev (nullable) the support.  1 <= B <= max_batch. */
+ * activities; s_dev (nullable) the support.  1 <= B <= max_batch.  The same call gives the same
+ * bits; the order of a support's fp64 sum follows from the layer's sizes and from B, so the same
+ * row in a batch of another size, or through bcpnn_predict, may differ in the last bit of its fp32
+ * support (and a class, where two supports are that close). */
 bcpnn_status bcpnn_forward(bcpnn_layer *layer, const float *x_dev, int32_t B, float *y_dev,
                            float *s_dev);
 

@@ -31,17 +31,18 @@
 //    for the next chunk's loads.  With one row tile they take most of a CU's LDS; where more
 //    workgroups than CUs follow one another, two of them share a CU with half of the stages each,
 //    for the widths that gain from it (two_per_cu).
-//  * A batch of many rows takes kR = 4: the weights are then loaded and converted once for four
-//    row tiles, and several workgroups share a CU, so that one's gather, softmax and stores pass
-//    under the others' products.
+//  * A batch of many rows may take kR = 4: the weights are then loaded and converted once for four
+//    row tiles, and two workgroups share a CU, so that one's gather, softmax and stores pass under
+//    the other's products.  Which form a launch takes is a matter of what its rounds of workgroups
+//    cost (launch_cost).
 //  * For a single row the matrix cores would compute 15 rows of padding: the same lanes then
 //    accumulate their own column and units with fp64 FMAs, and the lane groups are added.
 //  * The softmax of an HCU of up to 128 MCUs takes 16 lanes per row, four rows per wave: a third
 //    of the instructions of one row per wave.
-//  * Measured (MNIST-shaped layer, 156 active units x 100 MCUs x 30 HCUs; before: weights and input
-//    through registers, operand addresses in the product loop): batch 1 8.8 -> 6.3 us, batch 8192
-//    471 -> 270 us (28 TFLOP/s), training batch of 128 12.6 -> 11.9 us; 501 units x 70 MCUs x 17
-//    HCUs at 75 rows 28 -> 20 us; STL-shaped training batch 592 -> 535 us.
+//  * Measured, against weights and input through registers and operand addresses in the product loop
+//    (MNIST-shaped layer: 156 active units x 100 MCUs x 30 HCUs): batch 1 8.8 -> 6.5 us, batch 8192
+//    472 -> 267 us (28.8 TFLOP/s), training batch of 128 11.2 -> 9.7 us by its stamps; 501 units x 70
+//    MCUs x 17 HCUs at 75 rows 28.2 -> 19.5 us; STL-shaped training batch 609 -> 550 us.
 //  * In training, workgroups past the support's split the batch input into the contraction
 //    operands of the trace kernels, 16 rows x 64 columns per wave, beside the support.
 //
