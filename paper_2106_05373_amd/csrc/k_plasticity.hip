@@ -128,8 +128,8 @@ __device__ __forceinline__ bool better_high(double v, int32_t i, const Pick& p) 
 }
 
 // One workgroup per hidden HCU, a chain of strided reads of its score and mask columns: sixteen
-// waves, so that few of them follow one another (STL-shaped layer, 100 hidden HCUs: 81 us, with
-// four waves 111).  The HCU's mask column lives in LDS while it is edited: 1 = active, 0 = silent,
+// waves where the columns are long and the workgroups few, so that few reads follow one another
+// (STL-shaped layer, 100 hidden HCUs: 81 us, with four waves 111); else four.  The HCU's mask column lives in LDS while it is edited: 1 = active, 0 = silent,
 // 2 = silenced now, 3 = activated now (2 and 3 are excluded from the later swaps of this update).
 template <int kT>
 __global__ void __launch_bounds__(kT)
@@ -281,8 +281,11 @@ hipError_t launch_plasticity_swap(hipStream_t stream, const Geometry& g, const d
                                   float* w, int32_t* act_list, int32_t* act_count,
                                   int32_t* swap_count, hipEvent_t stop) {
     if (n_swaps > kMaxSwaps) return hipErrorInvalidValue;
-    // (2^22 workgroups of 1024 threads would be 2^32 work-items)
-    const bool wide = g.out_hcu < 1 << 22;
+    // Sixteen waves only where a thread of four would follow a long chain and every workgroup has a
+    // compute unit of its own.  The whole update with sixteen and with four waves, blocks of 2 x 4:
+    // 8000 input HCUs, 64 hidden 56 and 61 us, 200: 106 and 110, 256: 133 and 131; 1500 input HCUs,
+    // 4 hidden: 10.6 and 10.7, 100: 20.1 and 19.6; 784 and fewer input HCUs: four waves by 10 to 30%.
+    const bool wide = g.in_hcu >= 1536 && g.out_hcu < 256;
     return launch_timed(wide ? swap_kernel<kSwapThreads> : swap_kernel<kThreads>,
                         dim3((unsigned)g.out_hcu), dim3(wide ? kSwapThreads : kThreads),
                         (size_t)g.in_hcu, stream, nullptr, stop, g, mi, n_swaps, pi, pj,
