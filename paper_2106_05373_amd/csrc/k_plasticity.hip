@@ -35,11 +35,16 @@ constexpr int kMaxSwaps = 256;
 // by its residual to within a rounding of the division; the log takes a table (log_by_table).
 // STL-shaped layer (553 M terms): 0.99 ms, with a division and a log by division per term 1.47.
 // Without the log it takes 0.60, without the loads of Pij 0.80.  Two columns at a time: 8 to 10%
-// less than three, four or six (more registers, fewer waves) and 30% less than one; the columns
-// past the last full chunk go one by one, since an empty slot costs as much as a term.  The grid is
-// capped because each workgroup fills its table first.
+// less than three, four or six (more registers, fewer waves) and 30% less than one.  An empty slot
+// costs as much as a term, so of the columns past the last full chunk up to kGroup go one to a lane;
+// more go in one last pass of two, where the lanes without a second column read their first again
+// and drop it (as two loops, the lanes parted, ten columns took three columns' time: 30 x 100 onto
+// 10 x 10 units 67 us, now 34).  No unrolling: more registers leave five waves of a SIMD in flight for
+// six, 967 and 1163 us for the whole update of the STL-shaped layer, against 10% less for 100 rows.
+// The grid is capped because each workgroup fills its table first.
 constexpr int kGroup = 8;
 constexpr int kColChunk = 2;
+static_assert(kColChunk == 2, "the last pass holds two columns");
 constexpr int64_t kMiBlocks = 16384;
 __constant__ const LogTable kLogTable = log_table();
 
@@ -50,23 +55,27 @@ __device__ __forceinline__ double reciprocal(double x) {
     return fma(fma(-x, r, 1.0), r, r);
 }
 
-// The terms of kN columns (kGroup apart, all inside the block) and every row of a block; pj and
-// pij point at the first column.
-template <int kN>
+// The terms of kN columns (kGroup apart) and every row of a block; pj and pij point at the first
+// column.  kLast: the last of them is inside the block only where `has_last`.
+template <int kN, bool kLast = false>
 __device__ __forceinline__ double mi_columns(int in_mcu, int64_t n_out, const float* __restrict__ pi,
                                              const float* __restrict__ pj,
                                              const float* __restrict__ pij, double e,
-                                             const LogCell* cells, double part) {
+                                             const LogCell* cells, double part,
+                                             bool has_last = true) {
+    int at[kN];
     double pjc[kN], rj[kN];
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
-        pjc[k] = fmax((double)pj[k * kGroup], e);
+        at[k] = kLast && k == kN - 1 && !has_last ? 0 : k * kGroup;
+        pjc[k] = fmax((double)pj[at[k]], e);
         rj[k] = reciprocal(pjc[k]);
     }
+#pragma unroll 1
     for (int m = 0; m < in_mcu; ++m) {
         float q[kN];
 #pragma unroll
-        for (int k = 0; k < kN; ++k) q[k] = pij[m * n_out + k * kGroup];
+        for (int k = 0; k < kN; ++k) q[k] = pij[m * n_out + at[k]];
         const double pim = fmax((double)pi[m], e);
         const double ri = reciprocal(pim);
 #pragma unroll
@@ -74,7 +83,8 @@ __device__ __forceinline__ double mi_columns(int in_mcu, int64_t n_out, const fl
             const double v = fmax((double)q[k], e), den = pim * pjc[k], r = ri * rj[k];
             const double x0 = v * r;
             const double x = fma(fma(-den, x0, v), r, x0);
-            part = fma((double)q[k], log_by_table(x, cells), part);   // (0 log = 0)
+            const double sum = fma((double)q[k], log_by_table(x, cells), part);   // (0 log = 0)
+            part = kLast && k == kN - 1 && !has_last ? part : sum;
         }
     }
     return part;
@@ -102,10 +112,14 @@ mi_kernel(Geometry g, const float* __restrict__ pi, const float* __restrict__ pj
         const float* pj_b = pj + hj * g.out_mcu;
         const float* pij_b = pij + hi * g.in_mcu * g.n_out + hj * g.out_mcu;
         double part = 0.0;
-        int c = sub;
-        for (; c + (kColChunk - 1) * kGroup < g.out_mcu; c += kGroup * kColChunk)
+        int c = sub, left = g.out_mcu;                            // left: the same in every lane
+#pragma unroll 1
+        for (; left >= kGroup * kColChunk; c += kGroup * kColChunk, left -= kGroup * kColChunk)
             part = mi_columns<kColChunk>(g.in_mcu, g.n_out, pi_b, pj_b + c, pij_b + c, e, cells, part);
-        for (; c < g.out_mcu; c += kGroup)
+        if (left > kGroup)
+            part = mi_columns<kColChunk, true>(g.in_mcu, g.n_out, pi_b, pj_b + c, pij_b + c, e, cells,
+                                               part, sub < left - kGroup);
+        else if (sub < left)
             part = mi_columns<1>(g.in_mcu, g.n_out, pi_b, pj_b + c, pij_b + c, e, cells, part);
 #pragma unroll
         for (int off = kGroup / 2; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);

@@ -21,7 +21,7 @@ def _announce(request):
 @pytest.mark.parametrize("in_hcu,in_mcu,out_hcu,out_mcu", [
     (9, 2, 3, 1), (10, 1, 5, 3), (7, 3, 2, 8), (33, 2, 7, 9), (20, 2, 3, 16), (12, 10, 3, 17),
     (40, 2, 9, 24), (30, 3, 4, 33), (64, 2, 11, 100), (25, 2, 3, 257), (49152, 2, 8, 4),
-    (40, 2, 300, 5), (1535, 1, 3, 2), (1536, 1, 255, 1), (1536, 1, 256, 1),
+    (30, 5, 3, 10), (30, 5, 3, 15), (17, 2, 2, 25), (40, 2, 300, 5), (1535, 1, 3, 2), (1536, 1, 255, 1), (1536, 1, 256, 1),
 ])
 def test_scores_and_weights_on_any_state(in_hcu, in_mcu, out_hcu, out_mcu):
     rng = np.random.default_rng(in_hcu * 31 + out_mcu)
