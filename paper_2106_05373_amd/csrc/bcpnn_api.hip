@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <utility>
 #include <vector>
@@ -76,6 +77,7 @@ struct bcpnn_layer {
     hipStream_t side = nullptr;          // the layer's own stream for the silent-trace sweep
     int drop_bits = 0;
     int32_t max_active = 0;              // largest active count of a hidden HCU (swaps keep it)
+    int64_t n_active = 0;                // set mask entries (swaps keep it)
     float* pi[2] = {nullptr, nullptr};   // the trace kernel reads one and writes the other
     float* pj[2] = {nullptr, nullptr};
     int cur = 0;
@@ -451,6 +453,7 @@ bcpnn_status bcpnn_layer_create(const bcpnn_config* cfg, const uint8_t* mask_hos
 
     bcpnn_layer* L = new bcpnn_layer();
     L->max_active = max_active;
+    L->n_active = std::accumulate(count.begin(), count.end(), int64_t{0});
     L->full_mask = mask_is_full(*cfg, count);
     L->cfg = *cfg;
     L->g = Geometry{cfg->in_hcu, cfg->in_mcu, cfg->out_hcu, cfg->out_mcu,
@@ -643,10 +646,10 @@ bcpnn_status bcpnn_recompute_weights(bcpnn_layer* L) {
     HIP_TRY(L, join_side(L));
     hipEvent_t t0, t1;
     HIP_TRY(L, timer_events(L, BCPNN_KERNEL_WEIGHTS, &t0, &t1));
-    HIP_TRY(L, bcpnn::launch_recompute_weights(L->stream, L->g, L->act_list, L->act_count,
-                                               L->max_active, L->pi[L->cur], L->pj[L->cur], L->pij,
-                                               L->cfg.eps, L->cfg.bias_gain, L->drop_bits, L->w, L->b,
-                                               t0, t1));
+    HIP_TRY(L, bcpnn::launch_recompute_weights(L->stream, L->g, L->mask, L->act_list, L->act_count,
+                                               L->max_active, L->n_active, L->pi[L->cur],
+                                               L->pj[L->cur], L->pij, L->cfg.eps, L->cfg.bias_gain,
+                                               L->drop_bits, L->w, L->b, t0, t1));
     return BCPNN_OK;
 }
 
@@ -820,6 +823,7 @@ bcpnn_status bcpnn_set_state(bcpnn_layer* L, const bcpnn_state_view* v) {
     HIP_TRY(L, bcpnn::launch_apply_mask(L->stream, g, L->mask, L->w));
     HIP_TRY(L, hipStreamSynchronize(L->stream));
     L->max_active = max_active;
+    L->n_active = std::accumulate(count.begin(), count.end(), int64_t{0});
     L->full_mask = mask_is_full(L->cfg, count);
     L->mi_valid = false;
     return BCPNN_OK;

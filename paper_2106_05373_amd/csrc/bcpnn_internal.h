@@ -77,9 +77,10 @@ hipError_t launch_bias(hipStream_t stream, const Geometry& g, const float* pj, f
 
 // w = log(max(pij,eps) / (max(pi,eps) max(pj,eps))) on the active blocks (the silent ones hold 0
 // already, which every writer of w keeps), and b = bias_gain * log(max(pj, eps)).  max_active as for
-// launch_support.
-hipError_t launch_recompute_weights(hipStream_t stream, const Geometry& g, const int32_t* act_list,
-                                    const int32_t* act_count, int32_t max_active, const float* pi,
+// launch_support; n_active is the number of set mask entries.
+hipError_t launch_recompute_weights(hipStream_t stream, const Geometry& g, const uint8_t* mask,
+                                    const int32_t* act_list, const int32_t* act_count,
+                                    int32_t max_active, int64_t n_active, const float* pi,
                                     const float* pj, const float* pij, float eps, float bias_gain,
                                     int drop_bits, float* w, float* b, hipEvent_t start = nullptr,
                                     hipEvent_t stop = nullptr);

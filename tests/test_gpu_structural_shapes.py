@@ -56,3 +56,33 @@ def test_scores_and_weights_on_any_state(in_hcu, in_mcu, out_hcu, out_mcu):
     assert np.all(np.abs(pair.gpu.get_mi() - want) <= TOL_MI_REL * size)
     np.testing.assert_array_equal(pair.gpu.get_state()["mask"], pair.ora.mask)
     pair.close()
+
+
+# The weight pass over the whole matrix (dense masks, narrow blocks; 16-byte and scalar rows, rows past
+# one pass of a workgroup, full masks) and, with the sparser mask of the same layer, over the active
+# blocks.  Silent weights are exactly 0 either way.
+@pytest.mark.parametrize("in_hcu,in_mcu,out_hcu,out_mcu,share", [
+    (300, 2, 400, 3, 1.0), (300, 2, 400, 3, 0.5), (300, 2, 400, 3, 0.02), (512, 1, 333, 7, 0.9),
+    (2100, 1, 97, 33, 1.0), (2100, 1, 97, 33, 0.2), (600, 1, 1025, 1, 0.7), (530, 2, 2051, 4, 0.6),
+    (3000, 1, 2, 1024, 1.0), (1024, 3, 450, 50, 0.95),
+])
+def test_weights_under_masks_of_any_share(in_hcu, in_mcu, out_hcu, out_mcu, share):
+    rng = np.random.default_rng(in_hcu + out_mcu)
+    cfg = gpu_config(in_hcu, in_mcu, out_hcu, out_mcu, 16)
+    mask = (rng.random((in_hcu, out_hcu)) < share).astype(np.uint8)
+    mask[rng.integers(in_hcu), :] = 1
+    pair = Pair(cfg, mask)
+    st = pair.ora.get_state()
+    st["pi"] = rng.uniform(1e-9, 1.0, pair.n_in).astype(np.float32)
+    st["pj"] = rng.uniform(1e-9, 0.5, pair.n_out).astype(np.float32)
+    st["pij"] = rng.uniform(0.0, 0.3, (pair.n_in, pair.n_out)).astype(np.float32)
+    pair.gpu.set_state(st)
+    pair.ora.set_state(st)
+    pair.gpu.recompute_weights()
+    pair.ora.recompute_weights()
+    sg = pair.gpu.get_state()
+    assert_weights_close(sg["w"], pair.ora.w)
+    assert_weights_close(sg["b"], pair.ora.b)
+    silent = np.repeat(np.repeat(mask == 0, in_mcu, 0), out_mcu, 1)
+    assert not np.any(sg["w"].reshape(pair.n_in, pair.n_out)[silent])
+    pair.close()
