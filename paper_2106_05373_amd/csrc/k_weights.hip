@@ -185,10 +185,10 @@ unsigned sweep_blocks(const Geometry& g) {
 // blocks' rows, each fetched and stored once per block, amount to most of the matrix or more.  A
 // block's row of 4 out_mcu bytes begins at a multiple of the greatest common divisor of the two
 // lengths.  While Pij and w stay in the Infinity Cache a line fetched twice is cheap, so the active
-// blocks win up to 1.6 times the matrix (1.28 where a block's row is no multiple of 16 bytes: they
-// move 4 bytes per lane), beyond it up to 0.88.  Fewer than 512 rows, or rows that leave lanes of
-// a workgroup idle, hold the whole matrix back in proportion.  Whole and active blocks, us (1.0 = full
-// mask): 10000 x 3000 of 3 MCUs, 1.0: 57 and 158, 0.15: 56 and 81; 12000 x 10000 of 100 MCUs, 1.0:
+// blocks win up to 1.6 times the matrix, beyond it up to 0.88 (a fifth less where a block's row is no
+// multiple of 16 bytes: they move 4 bytes per lane; 2984 x 16000 of 50 MCUs, half set: 84 and 108 us).
+// Fewer than 512 rows, or rows that leave lanes of a workgroup idle, hold the whole matrix back in
+// proportion.  Whole and active blocks, us (1.0 = full mask): 10000 x 3000 of 3 MCUs, 1.0: 57 and 158, 0.15: 56 and 81; 12000 x 10000 of 100 MCUs, 1.0:
 // 193 and 266, 0.7: 185 and 204, 0.5: 186 and 159; 8000 x 7680 of 256 MCUs, 1.0: 102 and 105, 0.7:
 // 94 and 75; 1568 x 3000 of 100 MCUs, 1.0: 9.7 and 10.2, 0.7: 9.5 and 8.6; 3000 x 1650 of 33 MCUs,
 // 1.0: 12.5 and 22.6, 0.5: 11.9 and 13.2; 1200 x 800 of 4 MCUs, 1.0: 4.4 and 10.1, 0.15: 4.3 and 3.8.
@@ -197,7 +197,7 @@ bool whole_matrix(const Geometry& g, int64_t n_active) {
     const double lines = (row + 128 - step) / (double)row;            // (on average, over positions)
     const double share = lines * (double)n_active / ((double)g.in_hcu * g.out_hcu);
     const bool cached = (double)g.n_in * (double)g.n_out < 22e6;
-    const double most = !cached ? 0.88 : g.out_mcu % 4 == 0 ? 1.6 : 1.28;
+    const double most = (cached ? 1.6 : 0.88) * (g.out_mcu % 4 == 0 ? 1.0 : 0.8);
     return share > most * std::max(1.0, 512.0 / (double)g.n_in) * std::max(1.0, 768.0 / (double)g.n_out);
 }
 
