@@ -73,12 +73,12 @@ STL_WARMUP, STL_STEPS = 2, 16
 # kernel's sources (kernel_digest); a changed source reports null until measured again.  The
 # sweep's figure is for the counter run's average launch (MNIST shape: 7.65 batches per launch;
 # STL shape: 5.56), the others' for every launch (the support's for its training launches).
-_SWEEP_DIGEST = "342ee25aabaa250948e73a7a72b20b4b7cb948d0c39eb57713f4e3e7fe435f3c"
-_WEIGHT_DIGEST = "08fa27330640dbd5d42594d2f07db225b55682b7a522ef0ac8e9fd9816c3eebc"
-_SUPPORT_DIGEST = "677be2f8fe750f06651046dafab46907fb8748b6dc79a2e3a3a432a82000ac8c"
-MEASURED_TRAFFIC = {("mnist", _SWEEP_DIGEST): 93.05e6, ("stl", _SWEEP_DIGEST): 9823.33e6}
-MEASURED_WEIGHT_TRAFFIC = {("mnist", _WEIGHT_DIGEST): 4.63e6, ("stl", _WEIGHT_DIGEST): 263.93e6}
-MEASURED_SUPPORT_TRAFFIC = {("mnist", _SUPPORT_DIGEST): 11.63e6, ("stl", _SUPPORT_DIGEST): 957.27e6}
+_SWEEP_DIGEST = "eaa8d1189f685358533008098b533b56dbaff09e93a596b38aa6bcc23346fbd6"
+_WEIGHT_DIGEST = "d4a3a14e316b36e57671fbad471aba631accdaf10590a5b80039b9cf6a84cad3"
+_SUPPORT_DIGEST = "967ac4c2ac054eb0d48a4e87ba04941634ed11d5056638ccf80378664e10e473"
+MEASURED_TRAFFIC = {("mnist", _SWEEP_DIGEST): 92.76e6, ("stl", _SWEEP_DIGEST): 9719.35e6}
+MEASURED_WEIGHT_TRAFFIC = {("mnist", _WEIGHT_DIGEST): 4.63e6, ("stl", _WEIGHT_DIGEST): 263.94e6}
+MEASURED_SUPPORT_TRAFFIC = {("mnist", _SUPPORT_DIGEST): 11.63e6, ("stl", _SUPPORT_DIGEST): 956.69e6}
 
 
 def kernel_digest(csrc, files):
