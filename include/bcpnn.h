@@ -50,7 +50,9 @@
  * profiling off) into a HIP graph.  The layer's host-side bookkeeping (which trace and
  * operand buffers the next batch uses, which silent updates are queued) advances when a call
  * is made, so a captured sequence that ends with flush must be replayed exactly once, before
- * any later call on the layer.
+ * any later call on the layer.  Launches are laid out for the mask at capture (a structural update
+ * keeps what they depend on): after a set_state whose mask gives a hidden HCU more active inputs,
+ * capture again; a captured recompute_weights alone replays under any mask.
  *
  * Errors: every call returns a bcpnn_status.  Arguments are checked on the host before any
  * device work; BCPNN_EINVAL leaves the layer unchanged.  A failed HIP call returns

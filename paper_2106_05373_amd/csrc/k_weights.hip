@@ -63,35 +63,40 @@ recompute_active_kernel(Geometry g, const int32_t* __restrict__ act_list,
         }
         const int hj = work / per_hcu;
         const int rows_at_once = kSweepThreads / lanes;
-        const int r0 = (work % per_hcu) * rows_at_once * kWeightRows + threadIdx.x / lanes;
+        const int step = rows_at_once * kWeightRows;
         const int c0 = V * (threadIdx.x & (lanes - 1));
         const int k_total = act_count[hj] * g.in_mcu;
-        if (r0 >= k_total) continue;
         const int32_t* list = act_list + (int64_t)hj * g.in_hcu;
         const int64_t col0 = (int64_t)hj * g.out_mcu;
-        int64_t row[kWeightRows];
-        float pr[kWeightRows];
-#pragma unroll
-        for (int q = 0; q < kWeightRows; ++q) {
-            const int k = r0 + rows_at_once * q;
-            const int kk = k < k_total ? k : 0;
-            const int h = mcu_magic ? (int)__umulhi((uint32_t)kk, mcu_magic) : kk;
-            const int64_t i = (int64_t)list[h] * g.in_mcu + (kk - h * g.in_mcu);
-            pr[q] = pi[i];
-            row[q] = i * g.n_out + col0;
-        }
-        for (int c = c0; c < g.out_mcu; c += V * lanes) {
-            const vec pc = *reinterpret_cast<const vec*>(pj + col0 + c);
-            vec p[kWeightRows];
-#pragma unroll
-            for (int q = 0; q < kWeightRows; ++q) p[q] = *reinterpret_cast<const vec*>(pij + row[q] + c);
+        // (one pass, unless a captured launch is replayed under a mask of more active units)
+        for (int r0 = (work % per_hcu) * step + threadIdx.x / lanes; r0 < k_total;
+             r0 += per_hcu * step) {
+            int64_t row[kWeightRows];
+            float pr[kWeightRows];
 #pragma unroll
             for (int q = 0; q < kWeightRows; ++q) {
-                if (r0 + rows_at_once * q >= k_total) continue;
-                vec v;
+                const int k = r0 + rows_at_once * q;
+                const int kk = k < k_total ? k : 0;
+                const int h = mcu_magic ? (int)__umulhi((uint32_t)kk, mcu_magic) : kk;
+                const int64_t i = (int64_t)list[h] * g.in_mcu + (kk - h * g.in_mcu);
+                pr[q] = pi[i];
+                row[q] = i * g.n_out + col0;
+            }
+            for (int c = c0; c < g.out_mcu; c += V * lanes) {
+                const vec pc = *reinterpret_cast<const vec*>(pj + col0 + c);
+                vec p[kWeightRows];
 #pragma unroll
-                for (int e = 0; e < V; ++e) v[e] = round_storage(log_ratio(p[q][e], pr[q], pc[e], eps), drop);
-                *reinterpret_cast<vec*>(w + row[q] + c) = v;
+                for (int q = 0; q < kWeightRows; ++q)
+                    p[q] = *reinterpret_cast<const vec*>(pij + row[q] + c);
+#pragma unroll
+                for (int q = 0; q < kWeightRows; ++q) {
+                    if (r0 + rows_at_once * q >= k_total) continue;
+                    vec v;
+#pragma unroll
+                    for (int e = 0; e < V; ++e)
+                        v[e] = round_storage(log_ratio(p[q][e], pr[q], pc[e], eps), drop);
+                    *reinterpret_cast<vec*>(w + row[q] + c) = v;
+                }
             }
         }
     }

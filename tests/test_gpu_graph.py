@@ -12,7 +12,7 @@ import pytest
 
 from paper_2106_05373_amd import synth
 
-from pairs import bcpnn, workload_config, workload_mask
+from pairs import assert_weights_close, bcpnn, gpu_config, workload_config, workload_mask
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +94,39 @@ def test_captured_forward_replays_with_training_between():
         assert torch.equal(y_g, y_e), f"replay {rep}"
     lay.close()
     ref.close()
+
+
+@pytest.mark.parametrize("before,after", [(0.02, 0.5), (0.02, 1.0), (1.0, 0.02)])
+def test_captured_weight_pass_replays_under_a_later_mask(before, after):
+    """Sparse masks take the active blocks, dense ones the whole matrix; a replay follows the mask of
+    the state that it finds."""
+    import torch
+    rng = np.random.default_rng(3)
+    cfg = gpu_config(600, 2, 300, 4, 16)
+    masks = [(rng.random((600, 300)) < share).astype(np.uint8) for share in (before, after)]
+    for m in masks:
+        m[0, :] = 1
+    stream = torch.cuda.Stream()
+    lay = bcpnn().Layer(cfg, masks[0], stream=stream)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        lay.recompute_weights()
+    for k in (1, 0, 1):
+        st = lay.get_state()
+        st["mask"] = masks[k]
+        st["pij"] = rng.uniform(1e-6, 0.3, st["pij"].shape).astype(np.float32)
+        st["w"] = np.ones_like(st["w"])
+        lay.set_state(st)
+        with torch.cuda.stream(stream):
+            g.replay()
+        torch.cuda.synchronize()
+        got = lay.get_state()
+        lay.recompute_weights()
+        want = lay.get_state()
+        assert np.array_equal(got["w"], want["w"]) and np.array_equal(got["b"], want["b"])
+        active = np.repeat(np.repeat(masks[k], 2, 0), 4, 1).astype(bool)
+        assert not np.any(got["w"].reshape(active.shape)[~active])
+        pij = np.maximum(st["pij"].reshape(active.shape).astype(np.float64), cfg.eps)
+        ref = np.log(pij / np.outer(np.maximum(st["pi"], cfg.eps), np.maximum(st["pj"], cfg.eps)))
+        assert_weights_close(got["w"].reshape(active.shape)[active], ref[active])
+    lay.close()
